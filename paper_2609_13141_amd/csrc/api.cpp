@@ -185,7 +185,6 @@ struct Carve {
 struct AttnWs {
   void* kplain;
   void* ksum;
-  void* qplain;
   void* qhat;
   int32_t* sel;
   float* sel_bias;
@@ -206,7 +205,6 @@ AttnWs carve_attention(Carve& cv, const sas_config* c, int b, int n) {
   w.kplain = cv.take(kb);
   w.ksum = cv.take(kb);
   const size_t qb = (size_t)b * c->n_kv_heads * n * c->head_dim * ab;
-  w.qplain = cv.take(qb);
   w.qhat = cv.take(qb);
   w.sel = (int32_t*)cv.take(rows * 4);
   w.sel_bias = (float*)cv.take(rows * 4);
@@ -288,7 +286,7 @@ sas_status run_attention(const sas_config* c, int b, int n, const void* q, const
   if (need_sel) {
     if (w_gq) {  // projected gate queries are computed first; otherwise the select kernel sums the heads
       Timed tm("gate_query", s);
-      HIP_TRY(launch_gate_query(c->dtype, q, b, n, H, Hkv, dh, w_gq, ws.qplain, ws.qhat, s), "gate query");
+      HIP_TRY(launch_gate_query(c->dtype, q, b, n, H, Hkv, dh, w_gq, nullptr, ws.qhat, s), "gate query");
     }
     SelectArgs sa;
     sa.b = b;

@@ -117,7 +117,7 @@ hipError_t launch_block_summaries(int dtype, const void* K, int b, int n, int Hk
                                   const void* w_gk, void* kplain, void* ksum, hipStream_t s);
 // Gate queries qhat[b, Hkv, n, dh]: the group's query heads summed (fp64,
 // ascending head index) and rounded once; projected by w_gq when given (the
-// unprojected query then goes to `qplain`, scratch).
+// unprojected query then goes to `qplain`, unless that is null).
 hipError_t launch_gate_query(int dtype, const void* Q, int b, int n, int H, int Hkv, int dh, const void* w_gq,
                              void* qplain, void* qhat, hipStream_t s);
 // Per (b, group, query) selection (Top-K, gate, tau) against kbar.
