@@ -572,75 +572,216 @@ __global__ void attn_combine_kernel(AttnArgs P) {
   if (P.lse && c8 == 0) P.lse[((size_t)bi * P.H + h) * n + t] = (mu + log2f(l)) * LN2;
 }
 
-// ---- fp32: one thread per (batch, head, query), online softmax in fp32 ----
+// ---- fp32 path ------------------------------------------------------------------
+// How block m enters the attention of query t (fp32 path): attended, logit bias, value weight.
+struct F32Gate {
+  bool att;
+  float bias, w;
+};
+
+// One query with one wave, lane = head dimension (two per lane for dh = 128):
+// the path of queries that meet a non-finite value (see attn_f32_kernel).
 template <int DH>
-__global__ void attn_f32_kernel(AttnArgs P) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = P.n;
-  if (idx >= (size_t)P.b * P.H * n) return;
-  const int t = (int)(idx % n);
-  const int h = (int)((idx / n) % P.H);
-  const int bi = (int)(idx / ((size_t)n * P.H));
-  const int G = P.H / P.Hkv, g = h / G, B = P.B;
-  const float* q = (const float*)P.Q + (((size_t)bi * n + t) * P.H + h) * DH;
-  const float* Kg = (const float*)P.Kt;
-  const float* Vg = (const float*)P.V;
-  float qv[DH], acc[DH];
+__device__ void attn_f32_query(const AttnArgs& P, int bi, int h, int t, int lane) {
+  constexpr int NJ = DH / 64;
+  const int n = P.n, G = P.H / P.Hkv, g = h / G, B = P.B, beta = t / B, NB = (n + B - 1) / B;
+  const bool gated = P.mode == SAS_MODE_GATED, outer = gated && P.outer;
+  const size_t row = ((size_t)bi * P.Hkv + g) * n + t;
+  const size_t qo = (((size_t)bi * n + t) * P.H + h) * DH + lane;
+  float qv[NJ], acc[NJ];
 #pragma unroll
-  for (int j = 0; j < DH; ++j) {
-    qv[j] = q[j];
+  for (int j = 0; j < NJ; ++j) {
+    qv[j] = ((const float*)P.Q)[qo + j * 64];
     acc[j] = 0.f;
   }
   float mrun = -INFINITY, lrun = 0.f;
   auto visit = [&](int i, float bias, float w) {
-    const float* k = Kg + (((size_t)bi * n + i) * P.Hkv + g) * DH;
-    const float* v = Vg + (((size_t)bi * n + i) * P.Hkv + g) * DH;
+    const size_t ko = (((size_t)bi * n + i) * P.Hkv + g) * DH + lane;
     float z = 0.f;
 #pragma unroll
-    for (int j = 0; j < DH; ++j) z = fmaf(qv[j], k[j], z);
-    z = z * P.sm_scale + bias;
-    float mn = fmaxf(mrun, z);
-    float a = expf(mrun - mn), p = expf(z - mn);
+    for (int j = 0; j < NJ; ++j) z = fmaf(qv[j], ((const float*)P.Kt)[ko + j * 64], z);
+    z = wave_sum(z) * P.sm_scale + bias;
+    const float mn = fmaxf(mrun, z);
+    const float a = expf(mrun - mn), p = expf(z - mn);
     lrun = lrun * a + p;
-    const float pw = p * w;
 #pragma unroll
-    for (int j = 0; j < DH; ++j) acc[j] = acc[j] * a + pw * v[j];
+    for (int j = 0; j < NJ; ++j) acc[j] = acc[j] * a + p * w * ((const float*)P.V)[ko + j * 64];
     mrun = mn;
   };
-  const int beta = t / B;
-  const bool gated = P.mode == SAS_MODE_GATED;
-  const bool outer = gated && P.outer;
-  // log gate lg of a kept historical block -> (logit bias, value weight)
-  auto gate = [&](float lg, float& w) -> float {
-    w = outer ? expf(lg) : 1.f;
-    return outer ? 0.f : lg;
-  };
-  const size_t row = ((size_t)bi * P.Hkv + g) * n + t;
-  const int NB = (n + B - 1) / B;
   const int fb = doc_first(P.doc, bi, NB, t, B);
-  if (P.mode == SAS_MODE_DENSE) {
-    for (int i = fb * B; i <= t; ++i) visit(i, 0.f, 1.f);
-  } else if (gated && P.full) {
-    for (int m = fb; m < beta; ++m) {
-      float w;
-      const float bias = gate(P.gate_table[row * NB + m], w);
-      for (int i = m * B; i < (m + 1) * B; ++i) visit(i, bias, w);
-    }
-    for (int i = beta * B; i <= t; ++i) visit(i, 0.f, 1.f);
+  auto block = [&](int m, float lg) {
+    const float w = outer ? expf(lg) : 1.f;
+    for (int i = m * B; i < (m + 1) * B; ++i) visit(i, outer ? 0.f : lg, w);
+  };
+  if (P.mode == SAS_MODE_DENSE || (gated && P.full)) {
+    for (int m = fb; m < beta; ++m) block(m, gated ? P.gate_table[row * NB + m] : 0.f);
   } else {
     for (int k = 0; k < P.K; ++k) {
       const int m = P.sel[row * P.K + k];
       if (m < 0 || m >= beta) break;  // slots are ascending historical blocks, -1 padded
-      float w = 1.f, bias = 0.f;
-      if (gated) bias = gate(P.sel_bias[row * P.K + k], w);
-      for (int i = m * B; i < (m + 1) * B; ++i) visit(i, bias, w);
+      block(m, gated ? P.sel_bias[row * P.K + k] : 0.f);
     }
-    for (int i = beta * B; i <= t; ++i) visit(i, 0.f, 1.f);
   }
-  float* o = (float*)P.O + (((size_t)bi * n + t) * P.H + h) * DH;
+  for (int i = beta * B; i <= t; ++i) visit(i, 0.f, 1.f);
 #pragma unroll
-  for (int j = 0; j < DH; ++j) o[j] = acc[j] / lrun;
-  if (P.lse) P.lse[((size_t)bi * P.H + h) * n + t] = mrun + logf(lrun);
+  for (int j = 0; j < NJ; ++j) ((float*)P.O)[qo + j * 64] = acc[j] / lrun;
+  if (P.lse && lane == 0) P.lse[((size_t)bi * P.H + h) * n + t] = mrun + logf(lrun);
+}
+
+// fp32 attention: a workgroup owns 16 consecutive queries of one head (all in
+// one SAS block, B being a multiple of 16), its 4 waves take the 16-key tiles
+// in turn and their (max, sum, output) triples are merged in LDS at the end:
+// the sizes of this dtype are bound by latency, and 64 queries give 4 tiles a
+// wave at most.  v_mfma_f32_16x16x4_f32 throughout, operands straight from
+// global memory: S^T = K Q^T leaves query c = lane % 16 and the keys
+// 4 (lane / 16) + i in element i, which is the B operand of step i of
+// O^T += V^T P^T, so P never leaves its registers.  At 64 queries x 4 heads,
+// dh = 64: 7 us; one thread per query took 238 us.
+// A product with P = 0 would turn an infinite or NaN value of a key that a
+// query does not attend into NaN; tiles are checked for such values and the
+// workgroup's queries then take attn_f32_query, which reads attended keys only.
+template <int DH>
+__global__ void __launch_bounds__(256) attn_f32_kernel(AttnArgs P) {
+  constexpr int NC = DH / 16;
+  __shared__ float ml_s[4][2][16];
+  __shared__ float o_s[4][16][DH + 4];
+  __shared__ int bad_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, q = lane >> 4;
+  const int n = P.n, nqt = (n + 15) / 16;
+  const int qt = nqt - 1 - (int)(blockIdx.x % nqt);  // the longest rows first
+  const int h = (int)(blockIdx.x / nqt) % P.H, bi = (int)(blockIdx.x / nqt) / P.H;
+  const int G = P.H / P.Hkv, g = h / G, B = P.B;
+  const int t = min(qt * 16 + c, n - 1);
+  const int beta = (qt * 16) / B, NB = (n + B - 1) / B;
+  const bool gated = P.mode == SAS_MODE_GATED, dense = P.mode == SAS_MODE_DENSE;
+  const bool outer = gated && P.outer, full = gated && P.full;
+  const size_t row = ((size_t)bi * P.Hkv + g) * n + t;
+  const int fb = doc_first(P.doc, bi, NB, qt * 16, B);
+  if (tid == 0) bad_s = 0;
+  floatx4_t qv[NC];
+  {
+    const float* qp = (const float*)P.Q + (((size_t)bi * n + t) * P.H + h) * DH + 4 * q;
+#pragma unroll
+    for (int s = 0; s < NC; ++s) qv[s] = *(const floatx4_t*)(qp + 16 * s);
+  }
+  floatx4_t o[NC];
+#pragma unroll
+  for (int d = 0; d < NC; ++d) o[d] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  float mrun = -INFINITY, lrun = 0.f;
+  bool bad = false;
+  int cur = 0;  // this query's slot cursor: slots are ascending historical blocks, -1 padded
+  const int32_t* srow = P.sel + row * P.K;
+  const float* Kg = (const float*)P.Kt + ((size_t)bi * n * P.Hkv + g) * DH;
+  const float* Vg = (const float*)P.V + ((size_t)bi * n * P.Hkv + g) * DH;
+  const size_t kstride = (size_t)P.Hkv * DH;
+  for (int kt = fb * B / 16 + wave; kt <= qt; kt += 4) {
+    const int m = kt * 16 / B;
+    F32Gate gt = {m == beta || dense, 0.f, 1.f};
+    if (m < beta && !dense) {
+      float lg = 0.f;
+      if (full) {
+        gt.att = true;
+        lg = P.gate_table[row * NB + m];
+      } else {
+        int sm = -1;
+        while (cur < P.K && (sm = srow[cur]) >= 0 && sm < m) ++cur;
+        gt.att = cur < P.K && sm == m;
+        if (gt.att && gated) lg = P.sel_bias[row * P.K + cur];
+      }
+      if (gated && gt.att) {
+        gt.w = outer ? expf(lg) : 1.f;
+        gt.bias = outer ? 0.f : lg;
+      }
+    }
+    if (__builtin_amdgcn_ballot_w64(gt.att) == 0) continue;
+    const float* kp = Kg + (size_t)min(kt * 16 + c, n - 1) * kstride + 4 * q;
+    floatx4_t kv[NC];
+#pragma unroll
+    for (int s = 0; s < NC; ++s) kv[s] = *(const floatx4_t*)(kp + 16 * s);
+    float vv[4][NC];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* vp = Vg + (size_t)min(kt * 16 + 4 * q + i, n - 1) * kstride + c;
+#pragma unroll
+      for (int d = 0; d < NC; ++d) vv[i][d] = vp[16 * d];
+    }
+    floatx4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[s][e], qv[s][e], z, 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool on = gt.att && kt * 16 + 4 * q + i <= t;
+      z[i] = on ? z[i] * P.sm_scale + gt.bias : -INFINITY;
+      mx = fmaxf(mx, z[i]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(mrun, mx);
+    // a query with no finite logit so far keeps a zero sum
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float a = expf(mrun - ref);
+    float p[4], sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      p[i] = expf(z[i] - ref);
+      sum += p[i];
+      p[i] *= gt.w;
+    }
+    lrun = lrun * a + sum;  // this lane's keys; the four lane groups are added at the end
+    mrun = mn;
+#pragma unroll
+    for (int d = 0; d < NC; ++d)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[d][v] *= a;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int d = 0; d < NC; ++d) {
+        bad = bad || !(fabsf(vv[i][d]) < INFINITY);
+        o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][d], p[i], o[d], 0, 0, 0);
+      }
+  }
+  lrun += __shfl_xor(lrun, 16, 64);
+  lrun += __shfl_xor(lrun, 32, 64);
+  if (lane < 16) {
+    ml_s[wave][0][c] = mrun;
+    ml_s[wave][1][c] = lrun;
+  }
+#pragma unroll
+  for (int d = 0; d < NC; ++d) *(floatx4_t*)&o_s[wave][c][d * 16 + 4 * q] = o[d];
+  __syncthreads();
+  if (bad) bad_s = 1;
+  __syncthreads();
+  if (bad_s) {
+    for (int r = wave; r < 16 && qt * 16 + r < n; r += 4) attn_f32_query<DH>(P, bi, h, qt * 16 + r, lane);
+    return;
+  }
+  for (int idx = tid; idx < 16 * DH / 4; idx += 256) {
+    const int r = idx / (DH / 4), d0 = (idx % (DH / 4)) * 4;
+    if (qt * 16 + r >= n) continue;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, ml_s[w][0][r]);
+    const float ref = mx == -INFINITY ? 0.f : mx;
+    float l = 0.f;
+    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float a = expf(ml_s[w][0][r] - ref);
+      l += a * ml_s[w][1][r];
+      const floatx4_t ow = *(const floatx4_t*)&o_s[w][r][d0];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[v] += a * ow[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] /= l;
+    *(floatx4_t*)((float*)P.O + (((size_t)bi * n + qt * 16 + r) * P.H + h) * DH + d0) = acc;
+    if (P.lse && d0 == 0) P.lse[((size_t)bi * P.H + h) * n + qt * 16 + r] = mx + logf(l);
+  }
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
@@ -713,10 +854,9 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
       attn_combine_kernel<<<(unsigned)cdiv(rows, 256), 256, 0, s>>>(A);
     }
   } else {
-    size_t tot = (size_t)a.b * a.H * a.n;
-    unsigned grid = (unsigned)((tot + 127) / 128);
-    if (a.dh == 128) attn_f32_kernel<128><<<grid, 128, 0, s>>>(a);
-    else attn_f32_kernel<64><<<grid, 128, 0, s>>>(a);
+    const unsigned grid = (unsigned)cdiv(a.n, 16) * a.H * a.b;
+    if (a.dh == 128) attn_f32_kernel<128><<<grid, 256, 0, s>>>(a);
+    else attn_f32_kernel<64><<<grid, 256, 0, s>>>(a);
   }
   return hipGetLastError();
 }

@@ -1,6 +1,6 @@
 // C = A[M, K] * B[N, K]^T on MFMA (bf16 in, fp32 accumulate) with fused
 // epilogues: QKV projection + RoPE, SwiGLU (gate and up in one pass),
-// residual add.  A fp32 variant (plain FMA) serves the fp32 dtype.
+// residual add.  A variant on the fp32 MFMA serves the fp32 dtype.
 //
 // Epilogues that combine two output columns (RoPE rotates the pair
 // (i, i + dh/2) of a head; SwiGLU multiplies gate column f by up column f)
@@ -699,55 +699,161 @@ gemm_bf16_lds_kernel(GemmParams P) {
   }  // (the launch takes MI = 16 only for the shapes of the staged epilogue)
 }
 
-// ---- fp32 path: one thread per (row, logical pair or column) ----------------
-__global__ void gemm_f32_kernel(int epi, int M, int K, int N, int npairs, const float* __restrict__ A,
-                                const float* __restrict__ B0, const float* __restrict__ B1,
-                                const float* __restrict__ B2, const float* __restrict__ resid,
-                                float* out, float* out1, float* out2, int H, int Hkv, int dh,
-                                int seq_len, const float2* __restrict__ rope,
-                                const int32_t* __restrict__ row_pos) {
-  const bool plain = epi == EPI_RESID || epi == EPI_F32OUT;
-  const int cols = plain ? N : npairs;  // columns or pairs
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)M * cols) return;
-  const int row = (int)(idx / cols), c = (int)(idx % cols);
-  const float* a = A + (size_t)row * K;
-  if (plain) {
-    const float* b = B0 + (size_t)c * K;
-    float s = 0.f;
-    for (int k = 0; k < K; ++k) s = fmaf(a[k], b[k], s);
-    out[(size_t)row * N + c] = (epi == EPI_RESID ? resid[(size_t)row * N + c] : 0.f) + s;
-    return;
+// ---- fp32 path ------------------------------------------------------------------
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums, one rounding per addition).
+// Bound by latency at the sizes this dtype is used for (tens to a few thousand
+// rows of a narrow layer): a workgroup owns 16 FM rows x 16 FN logical columns
+// and its 4 waves split K, so that even a 64-row product has hundreds of waves
+// and a chain of K / 64 steps each; their sums meet in LDS in wave order.  The
+// operands go straight from global memory to registers, 16 bytes per lane: lane
+// (c, q) holds row or column c at k = 16 st + 4 q .. + 3, and step e multiplies
+// the k = 16 st + 4 q + e of the four lane groups.  At 64 rows of the d = 256,
+// d_ff = 688 layer the four products take 27 us; with one thread per output
+// they took 324 us.
+struct GemmF32 {
+  int M, K, N, npairs;
+  const float *A, *B0, *B1, *B2, *resid;
+  float *out, *out1, *out2;
+  int H, Hkv, dh, seq_len;
+  const float2* rope;
+  const int32_t* row_pos;
+};
+
+template <int EPI, int FM, int FN>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmF32 P) {
+  constexpr bool PLAIN = EPI == EPI_RESID || EPI == EPI_F32OUT;
+  static_assert(PLAIN || FN % 2 == 0, "column tiles 2u and 2u + 1 are the halves of pair group u");
+  __shared__ floatx4_t part[4][FM * FN][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, q = lane >> 4;
+  const int Mt = (P.M + 16 * FM - 1) / (16 * FM);
+  const int m0 = (blockIdx.x % Mt) * 16 * FM, nt = blockIdx.x / Mt;
+  const float* ar[FM];
+  const float* br[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) ar[i] = P.A + (size_t)min(m0 + i * 16 + c, P.M - 1) * P.K + 4 * q;
+#pragma unroll
+  for (int f = 0; f < FN; ++f) {
+    const float* r;
+    if constexpr (PLAIN) {
+      r = P.B0 + (size_t)min(nt * 16 * FN + f * 16 + c, P.N - 1) * P.K;
+    } else {
+      const int p = min(nt * 8 * FN + (f / 2) * 16 + c, P.npairs - 1);
+      r = b_row<float>(EPI, (p / 32) * 64 + p % 32 + (f & 1) * 32, P.N, P.npairs, P.K, P.B0, P.B1, P.B2, P.H, P.Hkv,
+                       P.dh);
+    }
+    br[f] = r + 4 * q;
   }
-  // logical pair c -> the two logical columns of the tile mapping
-  const int J = (c / 32) * 64 + (c % 32);
-  const float* b1 = b_row<float>(epi, J, N, npairs, K, B0, B1, B2, H, Hkv, dh);
-  const float* b2 = b_row<float>(epi, J + 32, N, npairs, K, B0, B1, B2, H, Hkv, dh);
-  float x1 = 0.f, x2 = 0.f;
-  for (int k = 0; k < K; ++k) {
-    x1 = fmaf(a[k], b1[k], x1);
-    x2 = fmaf(a[k], b2[k], x2);
+  floatx4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int f = 0; f < FN; ++f) acc[i][f] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // this wave's range of 16-deep steps; U steps are loaded together (K is a
+  // multiple of 4: a lane's 4 values are all inside K or all zero)
+  constexpr int U = FM == 1 ? 8 : (FM == 2 ? 4 : 2);
+  const int steps = (P.K + 15) / 16, per = (steps + 3) / 4;
+  const int s0 = wave * per, s1 = min(steps, s0 + per);
+  for (int st = s0; st < s1; st += U) {
+    floatx4_t a[U][FM], b[U][FN];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool ok = st + u < s1 && (st + u) * 16 + 4 * q < P.K;
+      const int k = ok ? (st + u) * 16 : 0;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        a[u][i] = *(const floatx4_t*)(ar[i] + k - (ok ? 0 : 4 * q));
+        if (!ok) a[u][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int f = 0; f < FN; ++f) {
+        b[u][f] = *(const floatx4_t*)(br[f] + k - (ok ? 0 : 4 * q));
+        if (!ok) b[u][f] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int f = 0; f < FN; ++f)
+            acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][f][e], acc[i][f], 0, 0, 0);
   }
-  if (epi == EPI_SWIGLU) {
-    out[(size_t)row * npairs + c] = silu_f(x1) * x2;
-    return;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int f = 0; f < FN; ++f) part[wave][i * FN + f][lane] = acc[i][f];
+  __syncthreads();
+  auto total = [&](int tile) {
+    floatx4_t t = part[0][tile][lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const floatx4_t p = part[w][tile][lane];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t[v] += p[v];
+    }
+    return t;
+  };
+  // element v of a tile: row 4 q + v, column c
+  constexpr int FU = PLAIN ? FN : FN / 2;
+  for (int u = wave; u < FM * FU; u += 4) {
+    const int i = u / FU, f = u % FU;
+    const int row0 = m0 + i * 16 + 4 * q;
+    if constexpr (PLAIN) {
+      const floatx4_t t = total(i * FN + f);
+      const int col = nt * 16 * FN + f * 16 + c;
+      if (col >= P.N) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (row0 + v >= P.M) continue;
+        const size_t o = (size_t)(row0 + v) * P.N + col;
+        P.out[o] = EPI == EPI_RESID ? P.resid[o] + t[v] : t[v];
+      }
+    } else {
+      const floatx4_t t1 = total(i * FN + 2 * f), t2 = total(i * FN + 2 * f + 1);
+      const int p = nt * 8 * FN + f * 16 + c;
+      if (p >= P.npairs) continue;
+      const int hh = P.dh / 2, hd = p / hh, ir = p % hh;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = row0 + v;
+        if (row >= P.M) continue;
+        float x1 = t1[v], x2 = t2[v];
+        if constexpr (EPI == EPI_SWIGLU) {
+          P.out[(size_t)row * P.npairs + p] = silu_f(x1) * x2;
+        } else {
+          float* dst;
+          if (hd < P.H) dst = P.out + ((size_t)row * P.H + hd) * P.dh;
+          else if (hd < P.H + P.Hkv) dst = P.out1 + ((size_t)row * P.Hkv + (hd - P.H)) * P.dh;
+          else dst = P.out2 + ((size_t)row * P.Hkv + (hd - P.H - P.Hkv)) * P.dh;
+          if (hd < P.H + P.Hkv) {
+            const int pos = P.row_pos ? P.row_pos[row] : row % P.seq_len;
+            const float2 cs = P.rope[(size_t)pos * hh + ir];
+            const float o1 = x1 * cs.x - x2 * cs.y;
+            const float o2 = x2 * cs.x + x1 * cs.y;
+            x1 = o1;
+            x2 = o2;
+          }
+          dst[ir] = x1;
+          dst[ir + hh] = x2;
+        }
+      }
+    }
   }
-  const int hh = dh / 2;
-  const int hd = c / hh, ir = c % hh;
-  float* dst;
-  if (hd < H) dst = out + ((size_t)row * H + hd) * dh;
-  else if (hd < H + Hkv) dst = out1 + ((size_t)row * Hkv + (hd - H)) * dh;
-  else dst = out2 + ((size_t)row * Hkv + (hd - H - Hkv)) * dh;
-  if (hd < H + Hkv) {
-    int pos = row_pos ? row_pos[row] : row % seq_len;
-    float2 cs = rope[(size_t)pos * hh + ir];
-    float o1 = x1 * cs.x - x2 * cs.y;
-    float o2 = x2 * cs.x + x1 * cs.y;
-    x1 = o1;
-    x2 = o2;
-  }
-  dst[ir] = x1;
-  dst[ir + hh] = x2;
+}
+
+template <int EPI>
+static hipError_t run_f32(const GemmF32& P, hipStream_t s) {
+  constexpr bool PLAIN = EPI == EPI_RESID || EPI == EPI_F32OUT;
+  const int nt = PLAIN ? cdiv(P.N, 32) : cdiv(P.npairs, 16);  // tiles of 32 logical columns
+  // taller tiles (fewer operand bytes per product) while two workgroups per compute unit remain
+  if ((long long)cdiv(P.M, 64) * nt >= 512) gemm_f32_kernel<EPI, 4, 2><<<cdiv(P.M, 64) * nt, 256, 0, s>>>(P);
+  else if ((long long)cdiv(P.M, 32) * nt >= 512) gemm_f32_kernel<EPI, 2, 2><<<cdiv(P.M, 32) * nt, 256, 0, s>>>(P);
+  else if constexpr (PLAIN) gemm_f32_kernel<EPI, 1, 1><<<cdiv(P.M, 16) * cdiv(P.N, 16), 256, 0, s>>>(P);
+  else gemm_f32_kernel<EPI, 1, 2><<<cdiv(P.M, 16) * nt, 256, 0, s>>>(P);
+  return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -802,13 +908,17 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   const bool plain = g.epi == EPI_RESID || g.epi == EPI_F32OUT;
   const int nlog = plain ? g.N : (npairs + 31) / 32 * 64;
   if (dtype == SAS_F32) {
-    const int cols = plain ? g.N : npairs;
-    size_t tot = (size_t)g.M * cols;
-    gemm_f32_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(
-        g.epi, g.M, g.K, nlog, npairs, (const float*)g.A, (const float*)g.B0, (const float*)g.B1,
-        (const float*)g.B2, (const float*)g.resid, (float*)g.out, (float*)g.out1, (float*)g.out2,
-        g.n_heads, g.n_kv_heads, g.head_dim, g.seq_len, g.rope, g.row_pos);
-    return hipGetLastError();
+    if (g.K % 4 != 0) return hipErrorInvalidValue;  // 16-byte operand loads (d and d_ff are multiples of 8)
+    const GemmF32 F = {g.M, g.K, plain ? g.N : nlog, npairs, (const float*)g.A, (const float*)g.B0,
+                       (const float*)g.B1, (const float*)g.B2, (const float*)g.resid, (float*)g.out,
+                       (float*)g.out1, (float*)g.out2, g.n_heads, g.n_kv_heads, g.head_dim, g.seq_len, g.rope,
+                       g.row_pos};
+    switch (g.epi) {
+      case EPI_QKV_ROPE: return run_f32<EPI_QKV_ROPE>(F, s);
+      case EPI_SWIGLU: return run_f32<EPI_SWIGLU>(F, s);
+      case EPI_F32OUT: return run_f32<EPI_F32OUT>(F, s);
+      default: return run_f32<EPI_RESID>(F, s);
+    }
   }
   if (!attrs_done) {
     (void)hipFuncSetAttribute((const void*)gemm_bf16_kernel<256, 256, 2, 4>,
