@@ -347,6 +347,25 @@ sas_status run_attention(const sas_config* c, int b, int n, const void* q, const
   return SAS_OK;
 }
 
+// Does a product of M rows take the weight-streaming kernel?  Up to 64 rows the
+// weights' bytes bound it; a tiled launch then has too few tiles to stream them
+// (32 rows, K = 18944, N = 3584: 28 workgroups, 140 us against 37 us).
+bool streams(int dtype, int M, int K) { return dtype == SAS_BF16 && M <= GEMV_MAX_ROWS && K % 128 == 0; }
+
+// Linear layer of the prefill and the MLP
+hipError_t linear(int dtype, const GemmArgs& g, hipStream_t s) {
+  return streams(dtype, g.M, g.K) ? launch_gemv(g, s) : launch_gemm(dtype, g, s);
+}
+
+// Linear layer of one row per sequence (decode): the rotary table is indexed by row
+hipError_t small_gemm(int dtype, GemmArgs g, hipStream_t s) {
+  g.seq_len = 0;
+  if (streams(dtype, g.M, g.K)) return launch_gemv(g, s);
+  g.seq_len = g.M;
+  g.row_pos = nullptr;
+  return launch_gemm(dtype, g, s);
+}
+
 sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer_weights* w, void* y,
                    const MlpWs& ws, hipStream_t s) {
   {
@@ -364,7 +383,7 @@ sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer
   g.out = ws.a;
   {
     Timed tm("gemm_gate_up", s);
-    HIP_TRY(launch_gemm(c->dtype, g, s), "gate/up gemm");
+    HIP_TRY(linear(c->dtype, g, s), "gate/up gemm");
   }
   GemmArgs d = {};
   d.epi = EPI_RESID;
@@ -377,7 +396,7 @@ sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer
   d.out = y;
   {
     Timed tm("gemm_down", s);
-    HIP_TRY(launch_gemm(c->dtype, d, s), "down gemm");
+    HIP_TRY(linear(c->dtype, d, s), "down gemm");
   }
   return SAS_OK;
 }
@@ -448,15 +467,6 @@ DecodeArgs decode_args(const sas_config* c, int b, const int32_t* pos, const sas
   d.w_gq = w ? w->w_gq : nullptr;
   d.w_gk = w ? w->w_gk : nullptr;
   return d;
-}
-
-// Linear layer of a few rows (decode): the streaming kernel when it applies,
-// else the tiled GEMM (rope table indexed by row).
-hipError_t small_gemm(int dtype, GemmArgs g, hipStream_t s) {
-  if (dtype == SAS_BF16 && g.M <= 16 && g.K % 128 == 0) return launch_gemv(g, s);
-  g.seq_len = g.M;
-  g.row_pos = nullptr;
-  return launch_gemm(dtype, g, s);
 }
 
 struct DecodeWs {
@@ -1133,7 +1143,7 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   g.prefill_cache = (cache && gemm_fills_cache(c->dtype, g)) ? &da : nullptr;
   {
     Timed tm("gemm_qkv", s);
-    HIP_TRY(launch_gemm(c->dtype, g, s), "qkv gemm");
+    HIP_TRY(linear(c->dtype, g, s), "qkv gemm");
   }
   SAS_TRY(run_attention(c, batch, seq_len, q, k, v, w->w_gq, w->w_gk, o, st.lse, st.k_summary, st.sel_idx,
                         st.log_gate, st.tau, lw.att, s, cache != nullptr));
@@ -1155,7 +1165,7 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   og.out = h1;
   {
     Timed tm("gemm_o", s);
-    HIP_TRY(launch_gemm(c->dtype, og, s), "o-proj gemm");
+    HIP_TRY(linear(c->dtype, og, s), "o-proj gemm");
   }
   return run_mlp(c, T, h1, w, y, lw.mlp, s);
 }
@@ -1244,7 +1254,7 @@ sas_status sas_decode_step(const sas_config* c, int32_t batch, const void* x, co
   // The first RMSNorm launch also writes the rotary rows of the positions.  On
   // the skinny-GEMM path the QKV product appends K/V to the cache itself
   // (unless a summary projection follows the append).
-  const bool gemv = c->dtype == SAS_BF16 && batch <= 16 && c->d_model % 128 == 0;
+  const bool gemv = streams(c->dtype, batch, c->d_model);
   const bool fused_append = gemv && !da.w_gk;
   // the packed copy of the weights, streamed by the skinny-GEMM path when given
   PackedLayout pl;

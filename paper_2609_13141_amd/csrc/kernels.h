@@ -91,8 +91,11 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 bool gemm_fills_cache(int dtype, const GemmArgs& a);
 
 // ---- gemv.hip --------------------------------------------------------------
-// The same products for M <= 16 rows (bf16, K % 128 == 0), streaming the
-// weights: rope is a per-row table [M, dh/2]; EPI_F32OUT writes fp32 A W^T.
+// The same products for M <= GEMV_MAX_ROWS rows (bf16, K % 128 == 0), streaming
+// the weights: rope is a per-row table [M, dh/2], or with seq_len > 0 (and no
+// append) that of positions row % seq_len, prefill_cache as in launch_gemm;
+// EPI_F32OUT (M <= 16) writes fp32 A W^T.
+constexpr int GEMV_MAX_ROWS = 64;
 hipError_t launch_gemv(const GemmArgs& a, hipStream_t s);
 // The packed decode layout of a product (see sas_pack_decode_weights): its
 // size in elements, and the kernel that writes it from the row-major B0..B2
