@@ -527,6 +527,11 @@ struct BwdWs {
   float* dlg_head_full;  // [b, H, n, NB] (full scope)
   float* dlg_slots;      // [b, Hkv, n, K] per-slot gradient when only the table is asked for
   uint32_t* queue;       // job counters of the pass kernels
+  int4* jobs;            // dK/dV jobs and the parts of divided key tiles (bf16, selections)
+  int* job_count;
+  int2* tile_part;
+  float* part;
+  BwdSplit split;
 };
 
 BwdWs carve_backward(Carve& cv, const sas_config* c, int b, int n) {
@@ -544,6 +549,12 @@ BwdWs carve_backward(Carve& cv, const sas_config* c, int b, int n) {
   w.dlg_head_full = full_grad(c) ? (float*)cv.take((size_t)b * H * n * NB * 4) : nullptr;
   w.dlg_slots = (float*)cv.take((size_t)b * Hkv * n * K * 4);
   w.queue = (uint32_t*)cv.take(256);
+  const bool lists = K > 0 && c->dtype == SAS_BF16 && c->mode != SAS_MODE_DENSE && !full_fwd(c);
+  w.split = lists ? bwd_split(b, c->n_kv_heads, n, c->block_size, c->top_k) : BwdSplit{0, 0};
+  w.jobs = lists ? (int4*)cv.take(((size_t)b * Hkv * ntk + w.split.slots) * sizeof(int4)) : nullptr;
+  w.job_count = lists ? (int*)cv.take(256) : nullptr;
+  w.tile_part = lists ? (int2*)cv.take((size_t)b * Hkv * ntk * sizeof(int2)) : nullptr;
+  w.part = lists ? (float*)cv.take((size_t)w.split.slots * 2 * 64 * c->head_dim * 4) : nullptr;
   return w;
 }
 
@@ -829,6 +840,12 @@ sas_status sas_attention_backward(const sas_config* c, int32_t batch, int32_t se
   a.tile_off = bw.tile_off;
   a.tile_rows = bw.tile_rows;
   a.queue = bw.queue;
+  a.jobs = bw.jobs;
+  a.job_count = bw.job_count;
+  a.tile_part = bw.tile_part;
+  a.part = bw.part;
+  a.split_chunks = bw.split.chunks;
+  a.split_slots = bw.split.slots;
   a.log_gate = gated ? in->log_gate : nullptr;
   a.outer = gated && c->gate_pos == SAS_GATE_OUTER;
   a.full = fullg;

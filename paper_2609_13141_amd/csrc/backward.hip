@@ -655,29 +655,89 @@ __global__ void __launch_bounds__(256) bwd_tile_rows_kernel(const uint32_t* __re
   if (!rows && tid == 0) cnt[tile] = total;
 }
 
-// exclusive prefix sum of the tile counts (one workgroup of 1024 threads; each
-// thread sums a contiguous range, then the ranges are offset in order)
-__global__ void __launch_bounds__(1024) bwd_rows_scan_kernel(const int* __restrict__ cnt, int T, int* __restrict__ off) {
-  __shared__ int part[1024];
-  const int tid = threadIdx.x;
-  const int per = (T + 1023) / 1024, lo = min(T, tid * per), hi = min(T, lo + per);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += cnt[i];
-  part[tid] = s;
-  __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int i = 0; i < 1024; ++i) {
-      const int v = part[i];
-      part[i] = run;
-      run += v;
-    }
+// exclusive sum over the 1024 threads of a workgroup; the total in `all`
+__device__ __forceinline__ int block_scan1024(int v, int* wsum, int& all) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
+  __syncthreads();  // wsum of an earlier call has been read
+  if (lane == 63) wsum[wave] = x;
   __syncthreads();
-  int run = part[tid];
+  int before = 0;
+  all = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    before += w < wave ? wsum[w] : 0;
+    all += wsum[w];
+  }
+  return before + x - v;
+}
+
+// Offsets of the tiles' row lists and the dK/dV jobs, in the order of the
+// passes: key tile by key tile (the longest lists first), (batch, group) pairs
+// inside.  cnt, off and tile_part are indexed [pair, tile].  One workgroup of
+// 1024 threads; each takes a contiguous range, then the ranges are offset.
+__global__ void __launch_bounds__(1024) bwd_jobs_kernel(const int* __restrict__ cnt, int Z, int ntiles, int chunks,
+                                                        int* __restrict__ off, int4* __restrict__ jobs,
+                                                        int* __restrict__ job_count, int2* __restrict__ tile_part) {
+  __shared__ int wsum[16];
+  const int T = Z * ntiles, tid = threadIdx.x;
+  const int per = (T + 1023) / 1024, lo = min(T, tid * per), hi = min(T, lo + per);
+  auto parts_of = [&](int c) {  // parts of a tile of c rows
+    const int ch = (c + 31) / 32;
+    return ch > chunks ? (ch + chunks - 1) / chunks : 1;
+  };
+  int s_row = 0, s_job = 0, s_slot = 0;
   for (int i = lo; i < hi; ++i) {
-    off[i] = run;
-    run += cnt[i];
+    const int c = cnt[(i % Z) * ntiles + i / Z], p = parts_of(c);
+    s_row += c;
+    s_job += p;
+    s_slot += p > 1 ? p : 0;
+  }
+  int all, jobs_all;
+  int row = block_scan1024(s_row, wsum, all);
+  int slot = block_scan1024(s_slot, wsum, all);
+  int job = block_scan1024(s_job, wsum, jobs_all);
+  if (tid == 0) *job_count = jobs_all;
+  for (int i = lo; i < hi; ++i) {
+    const int tile = (i % Z) * ntiles + i / Z;
+    const int c = cnt[tile], p = parts_of(c);
+    off[tile] = row;
+    tile_part[tile] = make_int2(p, slot);
+    for (int q = 0; q < p; ++q) jobs[job + q] = make_int4(tile, q, p, slot + q);
+    row += c;
+    job += p;
+    slot += p > 1 ? p : 0;
+  }
+}
+
+// dK and dV of the divided key tiles: their parts' sums added in order
+template <int DH>
+__global__ void __launch_bounds__(256) bwd_dkv_sum_kernel(const int2* __restrict__ tile_part,
+                                                          const float* __restrict__ part, int n, int Hkv, int ntiles,
+                                                          float sm, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+  const int2 tp = tile_part[blockIdx.x];
+  if (tp.x <= 1) return;
+  const int z = blockIdx.x / ntiles, k0 = (blockIdx.x % ntiles) * 64, g = z % Hkv, bi = z / Hkv;
+  const float* src = part + (size_t)tp.y * (2 * 64 * DH);
+  for (int i = threadIdx.x * 4; i < 2 * 64 * DH; i += 1024) {
+    const int which = i / (64 * DH), key = k0 + i / DH % 64, d = i % DH;
+    if (key >= n) continue;
+    float4 s = *(const float4*)(src + i);
+    for (int q = 1; q < tp.x; ++q) {
+      const float4 p = *(const float4*)(src + (size_t)q * (2 * 64 * DH) + i);
+      s.x += p.x;
+      s.y += p.y;
+      s.z += p.z;
+      s.w += p.w;
+    }
+    const float f = which ? 1.f : sm;
+    bf16_t* o = (which ? dV : dK) + (((size_t)bi * n + key) * Hkv + g) * DH + d;
+    *(uint2*)o = make_uint2(pack_bf16x2(s.x * f, s.y * f), pack_bf16x2(s.z * f, s.w * f));
   }
 }
 
@@ -697,7 +757,8 @@ __global__ void __launch_bounds__(1024) bwd_rows_scan_kernel(const int* __restri
 // dV^T += dO^T P, read in the accumulator's row permutation).  P and dS stay
 // in registers; the causal mask compares each key with its row's index.
 template <int DH, bool PLAIN>
-__device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int ktile, const int g, const int bi) {
+__device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int ktile, const int g, const int bi,
+                                                 const int part, const int parts, const int slot) {
   constexpr int NTH = 256, KT = 64;
   constexpr int KP = DH + 8;
   constexpr int QP = 32 + 4;
@@ -735,10 +796,12 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
   const size_t grow = ((size_t)bi * P.Hkv + g) * n;  // first row of (b, g) in [b, Hkv, n, ...]
   const int ntk = (n + KT - 1) / KT;
   int lbase = 0, lcnt = 0;
-  if (use_list) {
+  if (use_list) {  // this part of the tile's list: whole chunks
     const size_t tile = ((size_t)bi * P.Hkv + g) * ntk + ktile;
-    lbase = P.tile_off[tile];
-    lcnt = P.tile_cnt[tile];
+    const int cnt = P.tile_cnt[tile], ch = (cnt + 31) / 32, cp = (ch + parts - 1) / parts;
+    const int lo = min(cnt, part * cp * 32);
+    lbase = P.tile_off[tile] + lo;
+    lcnt = min(cnt - lo, cp * 32);
   }
   const int nchunk = use_list ? (lcnt + 31) / 32 : nqc;
 
@@ -979,6 +1042,19 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
     qc = nq;
     hg = nh;
   }
+  if (parts > 1) {  // fp32 sums of this part; bwd_dkv_sum_kernel adds the parts
+    float* kp = P.part + (size_t)slot * (2 * 64 * DH) + (size_t)(kh * 32 + lr) * DH + dhf * DHH;
+    float* vp = kp + 64 * DH;
+#pragma unroll
+    for (int dt = 0; dt < DHH / 32; ++dt)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int d0 = dt * 32 + 8 * v4 + 4 * lk;
+        *(float4*)(kp + d0) = make_float4(dk[dt][4 * v4], dk[dt][4 * v4 + 1], dk[dt][4 * v4 + 2], dk[dt][4 * v4 + 3]);
+        *(float4*)(vp + d0) = make_float4(dv[dt][4 * v4], dv[dt][4 * v4 + 1], dv[dt][4 * v4 + 2], dv[dt][4 * v4 + 3]);
+      }
+    return;
+  }
   if (!kvalid) return;
   const size_t off = (((size_t)bi * n + key) * P.Hkv + g) * DH + dhf * DHH;
   bf16_t* dkp = (bf16_t*)P.dK + off;
@@ -1001,12 +1077,19 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
 template <int DH, bool PLAIN>
 __global__ void __launch_bounds__(256, 2) bwd_dkv_bf16_kernel(BwdArgs P) {
   const int nkt = (P.n + 63) / 64, per = P.Hkv * P.b;
-  const int njobs = nkt * per;
+  const int njobs = P.tile_rows ? *P.job_count : nkt * per;
   for (int it = 0;; ++it) {
     const int job = P.queue ? queue_next_job(P.queue) : (it == 0 ? (int)blockIdx.x : njobs);
     if (job >= njobs) break;
-    const int r = job % per;  // the first (longest) key tiles first
-    bwd_dkv_bf16_job<DH, PLAIN>(P, job / per, r % P.Hkv, r / P.Hkv);
+    // the first (longest) key tiles first
+    if (P.tile_rows) {
+      const int4 j = P.jobs[job];
+      const int z = j.x / nkt;
+      bwd_dkv_bf16_job<DH, PLAIN>(P, j.x % nkt, z % P.Hkv, z / P.Hkv, j.y, j.z, j.w);
+    } else {
+      const int r = job % per;
+      bwd_dkv_bf16_job<DH, PLAIN>(P, job / per, r % P.Hkv, r / P.Hkv, 0, 1, 0);
+    }
   }
 }
 
@@ -1028,12 +1111,14 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
     bwd_selmask_kernel<<<(unsigned)cdiv(rows * NW, 256), 256, 0, s>>>(P.sel, rows, P.K, NW, P.selmask);
     if (!fullatt) {
       // each tile's list of attending rows: counts, offsets, rows
-      if (!P.tile_rows || !P.tile_cnt || !P.tile_off) return hipErrorInvalidValue;
+      if (!P.tile_rows || !P.tile_cnt || !P.tile_off || !P.jobs || !P.job_count || !P.tile_part || !P.part)
+        return hipErrorInvalidValue;
       const long long T = (long long)P.b * P.Hkv * ntk;
       if (T > INT32_MAX || rows * 2 * (P.K + 1) > (size_t)INT32_MAX) return hipErrorInvalidValue;
       const dim3 grid(ntk, P.Hkv, P.b);
       bwd_tile_rows_kernel<<<grid, 256, 0, s>>>(P.selmask, P.n, P.Hkv, P.B, NW, ntk, P.tile_cnt, nullptr, nullptr);
-      bwd_rows_scan_kernel<<<1, 1024, 0, s>>>(P.tile_cnt, (int)T, P.tile_off);
+      bwd_jobs_kernel<<<1, 1024, 0, s>>>(P.tile_cnt, P.b * P.Hkv, ntk, P.split_chunks, P.tile_off, P.jobs, P.job_count,
+                                         P.tile_part);
       bwd_tile_rows_kernel<<<grid, 256, 0, s>>>(P.selmask, P.n, P.Hkv, P.B, NW, ntk, P.tile_cnt, P.tile_off,
                                                 P.tile_rows);
       Q.tile_rows = P.tile_rows;
@@ -1057,7 +1142,10 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
                                                                              : bwd_dq_bf16_kernel<64, 4, false>);
   auto dkv = P.dh == 128 ? (plain ? bwd_dkv_bf16_kernel<128, true> : bwd_dkv_bf16_kernel<128, false>)
                          : (plain ? bwd_dkv_bf16_kernel<64, true> : bwd_dkv_bf16_kernel<64, false>);
-  const long long jq = (long long)cdiv(P.n, 128) * P.H * P.b, jk = (long long)ntk * P.Hkv * P.b;
+  const bool lists = Q.tile_rows != nullptr;
+  // list jobs are counted on the GPU: at most one per tile and one per slot
+  const long long jq = (long long)cdiv(P.n, 128) * P.H * P.b;
+  const long long jk = (long long)ntk * P.Hkv * P.b + (lists ? P.split_slots : 0);
   const int rq = resident_workgroups(dq, 256), rk = resident_workgroups(dkv, 256);
   if (rq <= 0 || rk <= 0 || jq > INT32_MAX || jk > INT32_MAX) return hipErrorInvalidValue;
   if (jq > rq || jk > rk) fill_f32_kernel<<<1, 64, 0, s>>>((float*)P.queue, 2, 0.f);  // job counters to zero
@@ -1066,6 +1154,15 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
   if (jq > 0) dq<<<(unsigned)std::min<long long>(jq, rq), 256, 0, s>>>(A);
   A.queue = jk > rk ? P.queue + 1 : nullptr;
   if (jk > 0) dkv<<<(unsigned)std::min<long long>(jk, rk), 256, 0, s>>>(A);
+  if (lists) {
+    const unsigned tiles = (unsigned)ntk * P.Hkv * P.b;
+    if (P.dh == 128)
+      bwd_dkv_sum_kernel<128><<<tiles, 256, 0, s>>>(P.tile_part, P.part, P.n, P.Hkv, ntk, P.sm_scale, (bf16_t*)P.dK,
+                                                    (bf16_t*)P.dV);
+    else
+      bwd_dkv_sum_kernel<64><<<tiles, 256, 0, s>>>(P.tile_part, P.part, P.n, P.Hkv, ntk, P.sm_scale, (bf16_t*)P.dK,
+                                                   (bf16_t*)P.dV);
+  }
   return hipGetLastError();
 }
 

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace sas {
 
 // Kernel-exact timing for the profiler: when `start` is set, the next launch
@@ -200,6 +202,15 @@ struct BwdArgs {
   int* tile_cnt;
   int* tile_off;
   int* tile_rows;
+  // the dK/dV pass's jobs (bf16 path, selections): a tile's row list in one or
+  // several parts of about split_chunks chunks of 32 rows; parts of a divided
+  // tile leave fp32 sums in `part` and are added afterwards
+  int4* jobs;             // [b Hkv ceil(n/64) + split_slots] (tile, part, parts, slot of the part)
+  int* job_count;         // [1]
+  int2* tile_part;        // [b, Hkv, ceil(n/64)] (parts, slot of the first)
+  float* part;            // [split_slots, 2, 64, dh] dK and dV of a part
+  int split_chunks;
+  long long split_slots;
   // gating formulation (GATED): outer gate; full scope; straight-through hard gate
   int outer, full, ste;
   float* dlog_gate_full;  // [b, Hkv, n, NB] output (full scope / straight-through)
@@ -209,6 +220,27 @@ struct BwdArgs {
 };
 // longest sequence of the bf16 attention backward (query chunks of 32 tracked in LDS)
 constexpr int BWD_MAX_SEQ = 262144;
+// How the dK/dV pass divides its row lists.  A key tile is attended by its own
+// rows and by every row that selected one of its blocks, so early tiles have
+// lists several times the average and, with few (batch, group) pairs, one of
+// them alone takes longer than the rest.  Parts of about 1/2048 of all chunks
+// (four for each of the 512 resident workgroups) and at least 8 chunks keep the
+// last wave short; a divided tile has at most twice chunks / split_chunks
+// parts, which bounds the slots.  28/4 heads, 5003 tokens, K = 32 (316 tiles):
+// the pass 1311 -> 512 us and 32 us for adding the parts.
+struct BwdSplit {
+  int chunks;
+  long long slots;
+};
+inline BwdSplit bwd_split(int b, int Hkv, int n, int B, int K) {
+  const long long Z = (long long)b * Hkv, tiles = Z * ((n + 63) / 64);
+  const long long rows = Z * n * (K + 1) * (B > 64 ? 2 : 1);  // list entries, at most
+  const long long all = rows / 32 + tiles;
+  BwdSplit r;
+  r.chunks = (int)std::max<long long>(8, (all + 2047) / 2048);
+  r.slots = 2 * all / r.chunks + 1;
+  return r;
+}
 hipError_t launch_attention_backward(int dtype, const BwdArgs& a, hipStream_t s);
 // p[0..n) = v with a kernel (capturable in a graph, unlike a memset node)
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
