@@ -558,42 +558,32 @@ BwdWs carve_backward(Carve& cv, const sas_config* c, int b, int n) {
   return w;
 }
 
-// Selector backward scratch.  The reductions over t (dkbar, dW_gq) and over
-// the batch (dW) go through split partials summed in a fixed order.
+// Selector backward scratch.  The reduction over t (dkbar and its counterpart of
+// the unprojected queries) and that over the batch (dW) go through split
+// partials summed in a fixed order.
 struct SelBwdWs {
   void* kplain;
   void* ksum;
   void* qplain;
   void* qhat;
   float* ds;
-  float* dqhat;
   float* dkbar;
+  float* s1;    // sum_t ds[t, m] qhat0[t] (for dW_gq)
   float* part;
 };
 
-// k splits of a reduction of length K feeding `tiles` output tiles per batch
-// entry, for Z entries: enough workgroups to fill the chip, each split >= 256
-int sel_bwd_splits(int tiles, int Z, int K) {
-  const int want = cdiv(1024, tiles * Z);
-  return std::max(1, std::min(want, cdiv(K, 256)));
-}
-
 struct SelBwdShape {
-  int NB, Z, s_dkbar, s_dwq, s_dwk;
-  size_t part_floats;
+  int NB, Z, splits;   // splits of the reduction over t: enough workgroups to fill the chip, each >= 256 rows
+  size_t part_floats;  // one matrix of partials
 };
 
 SelBwdShape sel_bwd_shape(const sas_config* c, int b, int n) {
   SelBwdShape h;
-  const int dh = c->head_dim, Hkv = c->n_kv_heads;
+  const size_t dh = c->head_dim;
   h.NB = cdiv(n, c->block_size);
-  h.Z = b * Hkv;
-  const int tdh = cdiv(dh, 64);
-  h.s_dkbar = sel_bwd_splits(cdiv(h.NB, 64) * tdh, h.Z, n);
-  h.s_dwq = sel_bwd_splits(tdh * tdh, h.Z, n);
-  h.s_dwk = sel_bwd_splits(tdh * tdh, h.Z, h.NB);
-  const size_t z = h.Z;
-  h.part_floats = std::max({z * h.s_dkbar * h.NB * dh, z * h.s_dwq * dh * dh, z * h.s_dwk * dh * dh});
+  h.Z = b * c->n_kv_heads;
+  h.splits = std::max(1, std::min(cdiv(1024, cdiv(h.NB, 64) * h.Z), cdiv(n, 256)));
+  h.part_floats = std::max((size_t)h.Z * h.splits * h.NB * dh, (size_t)h.Z * dh * dh);
   return h;
 }
 
@@ -606,9 +596,9 @@ SelBwdWs carve_selector_backward(Carve& cv, const sas_config* c, int b, int n) {
   w.qplain = cv.take((size_t)b * Hkv * n * dh * ab);
   w.qhat = cv.take((size_t)b * Hkv * n * dh * ab);
   w.ds = (float*)cv.take((size_t)b * Hkv * n * h.NB * 4);
-  w.dqhat = (float*)cv.take((size_t)b * Hkv * n * dh * 4);
   w.dkbar = (float*)cv.take((size_t)b * Hkv * h.NB * dh * 4);
-  w.part = (float*)cv.take(h.part_floats * 4);
+  w.s1 = (float*)cv.take((size_t)b * Hkv * h.NB * dh * 4);
+  w.part = (float*)cv.take(2 * h.part_floats * 4);
   return w;
 }
 
@@ -931,47 +921,51 @@ sas_status sas_selector_backward(const sas_config* c, int32_t batch, int32_t seq
   }
   // s = r / (G sqrt(dh)) with r = qhat . kbar
   const float dr_scale = 1.0f / ((float)(H / Hkv) * sqrtf((float)dh));
-  float* dqhat = out->dqhat ? out->dqhat : w.dqhat;
   float* dkbar = out->dkbar ? out->dkbar : w.dkbar;
   Timed tm("sel_bwd_gemm", s);
-  if (out->dqhat || dw_gq) {  // dqhat[t] = c sum_m ds[t, m] kbar[m]
+  if (out->dqhat) {  // dqhat[t] = c sum_m ds[t, m] kbar[m]
     SmallGemm g = {};
-    g.M = n, g.N = dh, g.K = NB, g.Z = h.Z, g.splits = 1, g.alpha = dr_scale;
-    g.A = ds, g.sAz = (long long)n * NB, g.sAi = NB, g.sAk = 1;
-    g.Bm = w.ksum, g.sBz = (long long)NB * dh, g.sBk = dh, g.sBj = 1;
-    g.C = dqhat, g.sCz = (long long)n * dh, g.sCs = 0, g.sCi = dh;
+    g.M = n, g.N = dh, g.K = NB, g.Z = h.Z, g.splits = 1, g.nmat = 1, g.alpha = dr_scale;
+    g.A = ds, g.sAz = (long long)n * NB, g.sAi = NB, g.sAk = 1, g.kmax_b = B;
+    g.Bm[0] = w.ksum, g.sBz = (long long)NB * dh, g.sBk = dh;
+    g.C[0] = out->dqhat, g.sCz = (long long)n * dh, g.sCi = dh, g.sCj = 1;
     HIP_TRY(launch_small_gemm(c->dtype, g, s), "dqhat");
   }
-  if (out->dkbar || dw_gk) {  // dkbar[m] = c sum_t ds[t, m] qhat[t]
+  // sums over t: dkbar[m] = c sum_t ds[t, m] qhat[t] and, for dW_gq, s1[m] = c sum_t ds[t, m] qhat0[t]
+  const bool need_dkbar = out->dkbar || dw_gk;
+  if (need_dkbar || dw_gq) {
     const size_t E = (size_t)NB * dh;
+    float* dst[2];
     SmallGemm g = {};
-    g.M = NB, g.N = dh, g.K = n, g.Z = h.Z, g.splits = h.s_dkbar, g.alpha = dr_scale;
-    g.A = ds, g.sAz = (long long)n * NB, g.sAi = 1, g.sAk = NB;
-    g.Bm = w.qhat, g.sBz = (long long)n * dh, g.sBk = dh, g.sBj = 1;
-    const bool direct = h.s_dkbar == 1;
-    g.C = direct ? dkbar : w.part, g.sCz = direct ? (long long)E : (long long)(E * h.s_dkbar), g.sCs = E, g.sCi = dh;
+    g.M = NB, g.N = dh, g.K = n, g.Z = h.Z, g.splits = h.splits, g.alpha = dr_scale;
+    g.A = ds, g.sAz = (long long)n * NB, g.sAi = 1, g.sAk = NB, g.kmin_b = B;
+    g.sBz = (long long)n * dh, g.sBk = dh;
+    if (need_dkbar) g.Bm[g.nmat] = w.qhat, dst[g.nmat++] = dkbar;
+    if (dw_gq) g.Bm[g.nmat] = w.qplain, dst[g.nmat++] = w.s1;
+    const bool direct = h.splits == 1;
+    for (int i = 0; i < g.nmat; ++i) g.C[i] = direct ? dst[i] : w.part + i * h.part_floats;
+    g.sCz = (long long)E * h.splits, g.sCs = E, g.sCi = dh, g.sCj = 1;
     HIP_TRY(launch_small_gemm(c->dtype, g, s), "dkbar");
-    if (!direct) HIP_TRY(launch_partial_sum(w.part, 1, h.Z, h.s_dkbar, E, dkbar, s), "dkbar sum");
+    if (!direct)
+      for (int i = 0; i < g.nmat; ++i)
+        HIP_TRY(launch_partial_sum(g.C[i], 1, h.Z, h.splits, E, dst[i], s), "dkbar sum");
   }
   const size_t E = (size_t)dh * dh;
-  if (dw_gq) {  // dW_gq[g] = sum_b sum_t dqhat[t]^T qhat0[t]
+  auto dw = [&](const float* a, const void* bm, long long ci, long long cj, float* out_dw) -> hipError_t {
+    // dW[g] = sum_b sum_m of products of row m of `a` and of `bm`
     SmallGemm g = {};
-    g.M = dh, g.N = dh, g.K = n, g.Z = h.Z, g.splits = h.s_dwq, g.alpha = 1.f;
-    g.A = dqhat, g.sAz = (long long)n * dh, g.sAi = 1, g.sAk = dh;
-    g.Bm = w.qplain, g.sBz = (long long)n * dh, g.sBk = dh, g.sBj = 1;
-    g.C = w.part, g.sCz = (long long)(E * h.s_dwq), g.sCs = E, g.sCi = dh;
-    HIP_TRY(launch_small_gemm(c->dtype, g, s), "dw_gq");
-    HIP_TRY(launch_partial_sum(w.part, batch, Hkv, h.s_dwq, E, dw_gq, s), "dw_gq sum");
-  }
-  if (dw_gk) {  // dW_gk[g] = sum_b sum_m dkbar[m]^T kbar0[m]
-    SmallGemm g = {};
-    g.M = dh, g.N = dh, g.K = NB, g.Z = h.Z, g.splits = h.s_dwk, g.alpha = 1.f;
-    g.A = dkbar, g.sAz = (long long)NB * dh, g.sAi = 1, g.sAk = dh;
-    g.Bm = w.kplain, g.sBz = (long long)NB * dh, g.sBk = dh, g.sBj = 1;
-    g.C = w.part, g.sCz = (long long)(E * h.s_dwk), g.sCs = E, g.sCi = dh;
-    HIP_TRY(launch_small_gemm(c->dtype, g, s), "dw_gk");
-    HIP_TRY(launch_partial_sum(w.part, batch, Hkv, h.s_dwk, E, dw_gk, s), "dw_gk sum");
-  }
+    g.M = dh, g.N = dh, g.K = NB, g.Z = h.Z, g.splits = 1, g.nmat = 1, g.alpha = 1.f;
+    g.A = a, g.sAz = (long long)NB * dh, g.sAi = 1, g.sAk = dh;
+    g.Bm[0] = bm, g.sBz = (long long)NB * dh, g.sBk = dh;
+    g.C[0] = batch == 1 ? out_dw : w.part, g.sCz = (long long)E, g.sCi = ci, g.sCj = cj;
+    const hipError_t e = launch_small_gemm(c->dtype, g, s);
+    if (e != hipSuccess || batch == 1) return e;
+    return launch_partial_sum(w.part, batch, Hkv, 1, E, out_dw, s);
+  };
+  // dW_gq[k, j] = sum_t dqhat[t, k] qhat0[t, j] = sum_m kbar[m, k] s1[m, j]: NB terms instead of n
+  if (dw_gq) HIP_TRY(dw(w.s1, w.ksum, 1, dh, dw_gq), "dw_gq");
+  // dW_gk[k, j] = sum_m dkbar[m, k] kbar0[m, j]
+  if (dw_gk) HIP_TRY(dw(dkbar, w.kplain, dh, 1, dw_gk), "dw_gk");
   return SAS_OK;
 }
 

@@ -1181,64 +1181,82 @@ hipError_t launch_gather_gate(const int32_t* sel, const float* log_gate, int b, 
 }
 
 // ---- selector ------------------------------------------------------------------
-// one wave per row (b, g, t); lane k < K holds slot k (per-slot input)
+// One wave per DS_ROWS consecutive rows (b, g, t), whose loads are issued
+// together; lane k < K holds slot k (per-slot input).  Bound by memory: log
+// gates and slots read, ds written.  A slot's gradient reaches its block's lane
+// through LDS (added there, so a block that appears twice counts twice).
+// 4 x 4096 rows, 32 groups, 64 blocks, K = 16: 119 us; exchanging the slots by
+// 2 K wave shuffles per 64 blocks took 214.
+constexpr int DS_ROWS = 4;
 __global__ void __launch_bounds__(256) selector_ds_kernel(const int32_t* __restrict__ sel,
                                                           const float* __restrict__ log_gate,
                                                           const float* __restrict__ dlog_gate,
                                                           const float* __restrict__ dfull, int act, int rows,
                                                           int n, int Hkv, int K, int B, int NB,
                                                           float* __restrict__ ds, const int32_t* __restrict__ doc) {
-  const int row = (int)(((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
-  if (row >= rows) return;
-  const int C = (row % n) / B;
-  const int F = doc_first(doc, row / (n * Hkv), NB, row % n, B);  // historical blocks are [F, C)
-  const float* lg = log_gate + (size_t)row * NB;
-  const float* dfr = dfull ? dfull + (size_t)row * NB : nullptr;
-  // every load of the row issued together (slot and its gradient, the first 64 log gates),
-  // masked afterwards, so the row costs one memory round trip
-  int sk = -1;
-  float dk = 0.f;
-  const bool has_slot = !dfr && lane < K;
-  {
-    const size_t so = (size_t)row * K + (has_slot ? lane : 0);
-    const int s0 = K > 0 && sel ? sel[so] : -1;
-    const float d0 = K > 0 && !dfr && dlog_gate ? dlog_gate[so] : 0.f;
-    if (has_slot && s0 >= 0) {
-      sk = s0;
-      dk = d0;
+  __shared__ float slot_s[4][DS_ROWS][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row0 = ((int)blockIdx.x * 4 + wave) * DS_ROWS;
+  if (row0 >= rows) return;
+  int sk[DS_ROWS], C[DS_ROWS], F[DS_ROWS];
+  float dk[DS_ROWS], lg0[DS_ROWS], D[DS_ROWS];
+  const bool has_slot = !dfull && K > 0 && lane < K;
+#pragma unroll
+  for (int r = 0; r < DS_ROWS; ++r) {
+    const int row = min(row0 + r, rows - 1);
+    sk[r] = -1;
+    dk[r] = 0.f;
+    if (has_slot) {
+      sk[r] = sel[(size_t)row * K + lane];
+      dk[r] = dlog_gate[(size_t)row * K + lane];
+    }
+    lg0[r] = log_gate[(size_t)row * NB + min(lane, NB - 1)];
+  }
+#pragma unroll
+  for (int r = 0; r < DS_ROWS; ++r) {
+    const int row = min(row0 + r, rows - 1);
+    C[r] = (row % n) / B;
+    F[r] = doc_first(doc, row / (n * Hkv), NB, row % n, B);  // historical blocks are [F, C)
+    if (sk[r] < 0) dk[r] = 0.f;
+    D[r] = 0.f;  // sum of the row's log-gate gradient (softmax)
+    if (act == SAS_ACT_SOFTMAX) {
+      float d = dk[r];
+      if (dfull)
+        for (int m = F[r] + lane; m < C[r]; m += 64) d += dfull[(size_t)row * NB + m];
+      D[r] = wave_sum(d);
     }
   }
-  const float lg0 = lg[min(lane, NB - 1)];
-  float D = 0.f;  // sum of the row's log-gate gradient (softmax)
-  if (act == SAS_ACT_SOFTMAX) {
-    if (dfr) {
-      for (int m = F + lane; m < C; m += 64) D += dfr[m];
-      D = wave_sum(D);
-    } else {
-      D = wave_sum(dk);
-    }
-  }
-  float* out = ds + (size_t)row * NB;
   for (int m0 = 0; m0 < NB; m0 += 64) {
     const int m = m0 + lane;
-    float dl = 0.f;
-    if (dfr) {
-      if (m < C && m >= F) dl = dfr[m];
-    } else {
-      for (int k = 0; k < K; ++k) {  // every lane shuffles (the sources must be active)
-        const int s = __shfl(sk, k, 64);
-        const float d = __shfl(dk, k, 64);
-        if (s == m) dl += d;
+    float dl[DS_ROWS], lg[DS_ROWS];
+#pragma unroll
+    for (int r = 0; r < DS_ROWS; ++r) {
+      const size_t o = (size_t)min(row0 + r, rows - 1) * NB + min(m, NB - 1);
+      lg[r] = m0 == 0 ? lg0[r] : log_gate[o];
+      if (dfull) {
+        const float d = dfull[o];
+        dl[r] = m < C[r] && m >= F[r] ? d : 0.f;
+      } else {
+        slot_s[wave][r][lane] = 0.f;
       }
     }
-    float v = 0.f;
-    if (m < C && m >= F) {
-      const float lgm = m0 == 0 ? lg0 : lg[m];
-      if (act == SAS_ACT_SOFTMAX) v = dl - expf(lgm) * D;
-      else if (act == SAS_ACT_SIGMOID) v = dl * (1.f - expf(lgm));
-      else v = dl;
+    if (!dfull) {  // a wave's LDS accesses complete in order
+#pragma unroll
+      for (int r = 0; r < DS_ROWS; ++r)
+        if (sk[r] >= m0 && sk[r] < m0 + 64) atomicAdd(&slot_s[wave][r][sk[r] - m0], dk[r]);
+#pragma unroll
+      for (int r = 0; r < DS_ROWS; ++r) dl[r] = slot_s[wave][r][lane];
     }
-    if (m < NB) out[m] = v;
+#pragma unroll
+    for (int r = 0; r < DS_ROWS; ++r) {
+      float v = 0.f;
+      if (m < C[r] && m >= F[r]) {
+        if (act == SAS_ACT_SOFTMAX) v = dl[r] - expf(lg[r]) * D[r];
+        else if (act == SAS_ACT_SIGMOID) v = dl[r] * (1.f - expf(lg[r]));
+        else v = dl[r];
+      }
+      if (m < NB && row0 + r < rows) ds[(size_t)(row0 + r) * NB + m] = v;
+    }
   }
 }
 
@@ -1248,104 +1266,112 @@ hipError_t launch_selector_ds(const int32_t* sel, const float* log_gate, const f
   const int rows = b * Hkv * n;
   if (rows <= 0) return hipSuccess;
   if (K > 64) return hipErrorInvalidValue;
-  selector_ds_kernel<<<cdiv(rows, 4), 256, 0, s>>>(sel, log_gate, dlog_gate, dlog_gate_full, act, rows, n, Hkv, K, B,
-                                                   cdiv(n, B), ds, doc);
+  if (K > 0 && !dlog_gate_full && (!sel || !dlog_gate)) return hipErrorInvalidValue;
+  selector_ds_kernel<<<cdiv(rows, 4 * DS_ROWS), 256, 0, s>>>(sel, log_gate, dlog_gate, dlog_gate_full, act, rows, n,
+                                                             Hkv, K, B, cdiv(n, B), ds, doc);
   return hipGetLastError();
 }
 
-// 64 x 64 output tile per workgroup, 16-deep k steps staged in LDS as fp32
-// (the next step's values loaded into registers during this step's FMAs);
-// thread (tx, ty) owns rows ty + 16 r and columns tx + 16 c.  Tile loads run
-// along whichever of the operand's two indices is contiguous.
-template <typename T>
+// 64 x N output tile per workgroup (N = dh) on v_mfma_f32_32x32x2_f32 (fp32
+// products, one rounding per addition), wave (wi, wj) 32 rows x N/2 columns;
+// 32-deep k stages in LDS as fp32 ([k][i] and [k][j]; pitches that put rows k
+// and k + 1, the two halves of an operand, in different banks, and 97 also the
+// transposed staging of a k-contiguous A), the next stage's values loaded into
+// registers during this one.  Loads of A run along its contiguous index.
+// ds^T [qhat0 | qhat], 4 x 4096 rows, 32 groups, 64 blocks, dh = 128: 179 us
+// for both (17 GFLOP); the VALU tile it replaces took 211 us for one.
+template <typename T, int DH>
 __global__ void __launch_bounds__(256) small_gemm_kernel(SmallGemm P) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int j0 = blockIdx.x * 64, i0 = blockIdx.y * 64;
+  constexpr int AP = 97, BP = DH + 32, TN = DH / 2, FN = TN / 32, NB8 = 32 * (DH / 8) / 256;
+  __shared__ float As[32 * AP];
+  __shared__ __align__(16) float Bs[32 * BP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lk = lane >> 5, wi = wave >> 1, wj = wave & 1;
+  const int i0 = blockIdx.x * 64, mat = blockIdx.y;
   const int z = blockIdx.z / P.splits, sp = blockIdx.z % P.splits;
-  const int kc = (P.K + P.splits - 1) / P.splits;
-  const int kb = sp * kc, ke = min(P.K, kb + kc);
+  // the k range that this tile's rows reach, then this split's share (whole stages)
+  const long long klo = P.kmin_b > 0 ? min((long long)P.K, (long long)(i0 + 1) * P.kmin_b) : 0;
+  const int khi = P.kmax_b > 0 ? min(P.K, min(P.M - 1, i0 + 63) / P.kmax_b) : P.K;
+  const int len = max(0, khi - (int)klo), kc = ((len + P.splits - 1) / P.splits + 31) / 32 * 32;
+  const int kb = (int)klo + sp * kc, ke = min(khi, kb + kc);
   const float* A = P.A + z * P.sAz;
-  const T* Bm = (const T*)P.Bm + z * P.sBz;
-  float acc[4][4];
+  const T* Bm = (const T*)P.Bm[mat] + z * P.sBz;
+  const bool icont = P.sAi == 1;
+  floatx16_t acc[FN];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int f = 0; f < FN; ++f)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
-  // the next k step's tile values are loaded into registers while this one is multiplied
-  float ra[4], rb[4];
+    for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+  float ra[8];
+  Vec8<T> rb[NB8];
   auto load = [&](int k0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < 8; ++e) {
       const int idx = tid + e * 256;
-      int ii, kk;
-      if (P.sAi == 1) {
-        ii = idx & 63;
-        kk = idx >> 6;
-      } else {
-        kk = idx & 15;
-        ii = idx >> 4;
-      }
-      const int i = i0 + ii, k = k0 + kk;
+      const int i = i0 + (icont ? idx & 63 : idx >> 5), k = k0 + (icont ? idx >> 6 : idx & 31);
       ra[e] = (i < P.M && k < ke) ? A[i * P.sAi + k * P.sAk] : 0.f;
-      int jj;
-      if (P.sBj == 1) {
-        jj = idx & 63;
-        kk = idx >> 6;
-      } else {
-        kk = idx & 15;
-        jj = idx >> 4;
-      }
-      const int j = j0 + jj, k2 = k0 + kk;
-      rb[e] = (j < P.N && k2 < ke) ? Act<T>::to_f32(Bm[j * P.sBj + k2 * P.sBk]) : 0.f;
     }
-  };
-  auto store = [&]() {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < NB8; ++e) {  // rows past the range repeat its last one (A is zero there)
       const int idx = tid + e * 256;
-      if (P.sAi == 1) As[idx >> 6][idx & 63] = ra[e];
-      else As[idx & 15][idx >> 4] = ra[e];
-      if (P.sBj == 1) Bs[idx >> 6][idx & 63] = rb[e];
-      else Bs[idx & 15][idx >> 4] = rb[e];
+      rb[e].load(Bm + (long long)min(k0 + idx / (DH / 8), ke - 1) * P.sBk + (idx % (DH / 8)) * 8);
     }
   };
   if (kb < ke) load(kb);
-  for (int k0 = kb; k0 < ke; k0 += 16) {
-    store();
+  for (int k0 = kb; k0 < ke; k0 += 32) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int idx = tid + e * 256;
+      As[icont ? (idx >> 6) * AP + (idx & 63) : (idx & 31) * AP + (idx >> 5)] = ra[e];
+    }
+#pragma unroll
+    for (int e = 0; e < NB8; ++e) {
+      const int idx = tid + e * 256;
+      float* d = Bs + (idx / (DH / 8)) * BP + (idx % (DH / 8)) * 8;
+      const bool in = k0 + idx / (DH / 8) < ke;  // (a repeated row may hold an infinity)
+      float x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = in ? rb[e].get(j) : 0.f;
+      *(float4*)d = make_float4(x[0], x[1], x[2], x[3]);
+      *(float4*)(d + 4) = make_float4(x[4], x[5], x[6], x[7]);
+    }
     __syncthreads();
-    if (k0 + 16 < ke) load(k0 + 16);
+    if (k0 + 32 < ke) load(k0 + 32);
+    // a wave whose rows are zero over the whole stage skips it
+    if (!(P.kmin_b > 0 && k0 + 31 < (long long)(i0 + wi * 32 + 1) * P.kmin_b)) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], bv[4];
+      for (int s = 0; s < 16; ++s) {
+        const float a = As[(2 * s + lk) * AP + wi * 32 + lr];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) a[r] = As[kk][ty + 16 * r];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bv[c] = Bs[kk][tx + 16 * c];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(a[r], bv[c], acc[r][c]);
+        for (int f = 0; f < FN; ++f)
+          acc[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, Bs[(2 * s + lk) * BP + wj * TN + f * 32 + lr], acc[f], 0, 0, 0);
+      }
     }
     __syncthreads();
   }
-  float* C = P.C + z * P.sCz + sp * P.sCs;
+  float* C = P.C[mat] + z * P.sCz + sp * P.sCs;
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int f = 0; f < FN; ++f)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + ty + 16 * r, j = j0 + tx + 16 * c;
-      if (i < P.M && j < P.N) C[i * P.sCi + j] = P.alpha * acc[r][c];
+    for (int v = 0; v < 16; ++v) {
+      const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * lk + (v & 3), j = wj * TN + f * 32 + lr;
+      if (i < P.M) C[i * P.sCi + j * P.sCj] = P.alpha * acc[f][v];
     }
 }
 
 hipError_t launch_small_gemm(int dtype, const SmallGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.Z <= 0) return hipSuccess;
-  if (g.splits < 1 || (size_t)g.Z * g.splits > 65535) return hipErrorInvalidValue;
-  dim3 grid(cdiv(g.N, 64), cdiv(g.M, 64), g.Z * g.splits);
-  if (dtype == SAS_BF16) small_gemm_kernel<bf16_t><<<grid, 256, 0, s>>>(g);
-  else small_gemm_kernel<float><<<grid, 256, 0, s>>>(g);
+  if (g.splits < 1 || (g.N != 64 && g.N != 128) || (g.sAi != 1 && g.sAk != 1) || g.nmat < 1 || g.nmat > 2)
+    return hipErrorInvalidValue;
+  if ((size_t)g.Z * g.splits > 65535) return hipErrorInvalidValue;
+  dim3 grid(cdiv(g.M, 64), g.nmat, g.Z * g.splits);
+  if (dtype == SAS_BF16) {
+    if (g.N == 128) small_gemm_kernel<bf16_t, 128><<<grid, 256, 0, s>>>(g);
+    else small_gemm_kernel<bf16_t, 64><<<grid, 256, 0, s>>>(g);
+  } else {
+    if (g.N == 128) small_gemm_kernel<float, 128><<<grid, 256, 0, s>>>(g);
+    else small_gemm_kernel<float, 64><<<grid, 256, 0, s>>>(g);
+  }
   return hipGetLastError();
 }
 

@@ -257,18 +257,22 @@ hipError_t launch_gather_gate(const int32_t* sel, const float* log_gate, int b, 
 hipError_t launch_selector_ds(const int32_t* sel, const float* log_gate, const float* dlog_gate,
                               const float* dlog_gate_full, int act, int b, int n, int Hkv, int K, int B, float* ds,
                               const int32_t* doc, hipStream_t s);
-// C(z, split)[i, j] = alpha sum_{k in split} A(z)[i, k] B(z)[k, j] for z < Z: fp32
-// A, B in the activation dtype, fp32 C; strides in elements.  With splits > 1
-// each split writes its own partial at C + split * sCs.
+// C(mat, z, split)[i, j] = alpha sum_{k in split} A(z)[i, k] B(mat, z)[k, j] for
+// mat < nmat, z < Z, j < N = 64 or 128: fp32 A with sAi = 1 or sAk = 1, B of the
+// activation dtype with rows of N values, fp32 C; strides in elements.  With
+// splits > 1 each split writes its own partial at C + split * sCs.  kmin_b > 0:
+// A[i, k] is zero for k < (i + 1) kmin_b; kmax_b > 0: zero for k >= i / kmax_b
+// (the parts of ds that no row reaches are not read).
 struct SmallGemm {
-  int M, N, K, Z, splits;
+  int M, N, K, Z, splits, nmat;
   float alpha;
   const float* A;
   long long sAz, sAi, sAk;
-  const void* Bm;
-  long long sBz, sBk, sBj;
-  float* C;
-  long long sCz, sCs, sCi;
+  const void* Bm[2];
+  long long sBz, sBk;
+  float* C[2];
+  long long sCz, sCs, sCi, sCj;
+  int kmin_b, kmax_b;
 };
 hipError_t launch_small_gemm(int dtype, const SmallGemm& g, hipStream_t s);
 // out[zo, e] = sum_{u < U} sum_{q < S} part[((u ZO + zo) S + q) E + e]
