@@ -182,6 +182,11 @@ struct Carve {
   }
 };
 
+// Does a product of M rows take the weight-streaming kernel?  Up to 64 rows the
+// weights' bytes bound it; a tiled launch then has too few tiles to stream them
+// (32 rows, K = 18944, N = 3584: 28 workgroups, 140 us against 37 us).
+bool streams(int dtype, int M, int K) { return dtype == SAS_BF16 && M <= GEMV_MAX_ROWS && K % 128 == 0; }
+
 struct AttnWs {
   void* kplain;
   void* ksum;
@@ -232,6 +237,38 @@ MlpWs carve_mlp(Carve& cv, const sas_config* c, size_t T) {
   return w;
 }
 
+// Scratch of the tiled products over T rows whose K is split (0 when none is):
+// the MLP's two and, with `attn`, the QKV and O projections; used one at a time.
+size_t gemm_part_bytes(const sas_config* c, size_t T, bool attn) {
+  size_t most = 0;
+  auto product = [&](int epi, int N, int K) {
+    GemmArgs g = {};
+    g.epi = epi;
+    g.M = (int)T;
+    g.N = N;
+    g.K = K;
+    g.head_dim = c->head_dim;
+    if (!streams(c->dtype, g.M, K)) most = std::max(most, gemm_scratch_bytes(c->dtype, g));
+  };
+  product(EPI_SWIGLU, c->d_ff, c->d_model);
+  product(EPI_RESID, c->d_model, c->d_ff);
+  if (attn) {
+    product(EPI_QKV_ROPE, (c->n_heads + 2 * c->n_kv_heads) * c->head_dim, c->d_model);
+    product(EPI_RESID, c->d_model, c->n_heads * c->head_dim);
+  }
+  return most;
+}
+
+struct GemmPart {
+  float* p;
+  size_t bytes;
+};
+
+GemmPart carve_gemm_part(Carve& cv, const sas_config* c, size_t T, bool attn) {
+  const size_t n = gemm_part_bytes(c, T, attn);
+  return {n ? (float*)cv.take(n) : nullptr, n};
+}
+
 struct LayerWs {
   void* u1;
   float2* rope;
@@ -243,6 +280,7 @@ struct LayerWs {
   void* h1;
   AttnWs att;
   MlpWs mlp;
+  GemmPart part;
 };
 
 LayerWs carve_layer(Carve& cv, const sas_config* c, int b, int n) {
@@ -260,6 +298,7 @@ LayerWs carve_layer(Carve& cv, const sas_config* c, int b, int n) {
   w.h1 = cv.take(T * c->d_model * ab);
   w.att = carve_attention(cv, c, b, n);
   w.mlp = carve_mlp(cv, c, T);
+  w.part = carve_gemm_part(cv, c, T, true);
   return w;
 }
 
@@ -347,11 +386,6 @@ sas_status run_attention(const sas_config* c, int b, int n, const void* q, const
   return SAS_OK;
 }
 
-// Does a product of M rows take the weight-streaming kernel?  Up to 64 rows the
-// weights' bytes bound it; a tiled launch then has too few tiles to stream them
-// (32 rows, K = 18944, N = 3584: 28 workgroups, 140 us against 37 us).
-bool streams(int dtype, int M, int K) { return dtype == SAS_BF16 && M <= GEMV_MAX_ROWS && K % 128 == 0; }
-
 // Linear layer of the prefill and the MLP
 hipError_t linear(int dtype, const GemmArgs& g, hipStream_t s) {
   return streams(dtype, g.M, g.K) ? launch_gemv(g, s) : launch_gemm(dtype, g, s);
@@ -367,7 +401,7 @@ hipError_t small_gemm(int dtype, GemmArgs g, hipStream_t s) {
 }
 
 sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer_weights* w, void* y,
-                   const MlpWs& ws, hipStream_t s) {
+                   const MlpWs& ws, const GemmPart& part, hipStream_t s) {
   {
     Timed tm("rmsnorm", s);
     HIP_TRY(launch_rmsnorm(c->dtype, x, w->rms2, ws.u2, (int)T, c->d_model, c->rms_eps, s), "rmsnorm");
@@ -381,6 +415,8 @@ sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer
   g.B1 = w->w_up;
   g.N = c->d_ff;
   g.out = ws.a;
+  g.part = part.p;
+  g.part_bytes = part.bytes;
   {
     Timed tm("gemm_gate_up", s);
     HIP_TRY(linear(c->dtype, g, s), "gate/up gemm");
@@ -394,6 +430,8 @@ sas_status run_mlp(const sas_config* c, size_t T, const void* x, const sas_layer
   d.N = c->d_model;
   d.resid = x;
   d.out = y;
+  d.part = part.p;
+  d.part_bytes = part.bytes;
   {
     Timed tm("gemm_down", s);
     HIP_TRY(linear(c->dtype, d, s), "down gemm");
@@ -734,6 +772,7 @@ size_t sas_workspace_size(const sas_config* c, int32_t op, int32_t batch, int32_
     case SAS_OP_MLP:
       if (check_config(c, true) != SAS_OK) return 0;
       carve_mlp(cv, c, (size_t)batch);
+      carve_gemm_part(cv, c, (size_t)batch, false);
       break;
     case SAS_OP_LAYER:
       if (seq_len <= 0 || check_config(c, true) != SAS_OK) return 0;
@@ -1082,8 +1121,9 @@ sas_status sas_mlp_forward(const sas_config* c, int32_t tokens, const void* x, c
   SAS_TRY(check_weights(w, false, true));
   Carve cv(ws);
   MlpWs mw = carve_mlp(cv, c, (size_t)tokens);
+  const GemmPart part = carve_gemm_part(cv, c, (size_t)tokens, false);
   SAS_TRY(check_ws(ws, ws_bytes, cv.off));
-  return run_mlp(c, (size_t)tokens, x, w, y, mw, (hipStream_t)stream);
+  return run_mlp(c, (size_t)tokens, x, w, y, mw, part, (hipStream_t)stream);
 }
 
 sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len, const void* x,
@@ -1151,6 +1191,8 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   g.rope = lw.rope;
   // with a cache, the QKV product writes the K/V pages itself where it can
   const DecodeArgs da = cache ? decode_args(c, batch, nullptr, cache, w) : DecodeArgs{};
+  g.part = lw.part.p;
+  g.part_bytes = lw.part.bytes;
   g.prefill_cache = (cache && gemm_fills_cache(c->dtype, g)) ? &da : nullptr;
   {
     Timed tm("gemm_qkv", s);
@@ -1174,11 +1216,13 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   og.N = c->d_model;
   og.resid = x;
   og.out = h1;
+  og.part = lw.part.p;
+  og.part_bytes = lw.part.bytes;
   {
     Timed tm("gemm_o", s);
     HIP_TRY(linear(c->dtype, og, s), "o-proj gemm");
   }
-  return run_mlp(c, T, h1, w, y, lw.mlp, s);
+  return run_mlp(c, T, h1, w, y, lw.mlp, lw.part, s);
 }
 
 size_t sas_decode_packed_bytes(const sas_config* c) {

@@ -9,8 +9,6 @@
 // half (J/32)%2.  A 32x32 MFMA output tile holds column J%32 in lane J%32, so
 // the two halves of a pair sit in neighbouring 32-column subtiles of the same
 // lane.  Plain (residual) GEMMs use the identity mapping.
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
 
@@ -31,11 +29,15 @@ struct GemmParams {
   const float2* rope;
   const int32_t* row_pos;
   int group_m;       // M tiles per group of the tile order (0: M-fastest over all tiles, no XCD remap)
-  int n_off, n_cnt;  // gemm_bf16_lds_kernel: logical columns [n_off, n_off + n_cnt) of this launch
   // prefill cache write of the staged QKV epilogue (NULL k_pages: none)
   bf16_t* k_pages;
   bf16_t* v_pages;
   PageGeom geom;
+  // K split over several workgroups per tile: each leaves its fp32 accumulators in
+  // part [splits, tiles][BM x BN] (in the accumulators' own order) and
+  // gemm_finish_kernel adds them and runs the epilogue
+  int splits;
+  float* part;
 };
 
 // Tile of workgroup `bid`.  Workgroups are dispatched round-robin over the 8
@@ -43,6 +45,14 @@ struct GemmParams {
 // range of a grouped tile order -- groups of group_m M tiles, M fastest inside
 // a group -- so the workgroups sharing an L2 share operand tiles instead of
 // each XCD streaming the whole weight matrix.
+__device__ __forceinline__ void grouped_tile(int lid, int Mt, int Nt, int group_m, int& mt, int& nt) {
+  const int gm = min(group_m, Mt);
+  const int per_group = gm * Nt, grp = lid / per_group, m_first = grp * gm;
+  const int gsz = min(Mt - m_first, gm), in = lid - grp * per_group;
+  mt = m_first + in % gsz;
+  nt = in / gsz;
+}
+
 __device__ __forceinline__ void tile_of(int bid, int Mt, int Nt, int group_m, int& mt, int& nt) {
   if (group_m <= 0) {
     mt = bid % Mt;
@@ -51,11 +61,7 @@ __device__ __forceinline__ void tile_of(int bid, int Mt, int Nt, int group_m, in
   }
   const int T = Mt * Nt, q = T / 8, r = T % 8, x = bid % 8, loc = bid / 8;
   const int lid = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + loc;
-  const int gm = min(group_m, Mt);
-  const int per_group = gm * Nt, grp = lid / per_group, m_first = grp * gm;
-  const int gsz = min(Mt - m_first, gm), in = lid - grp * per_group;
-  mt = m_first + in % gsz;
-  nt = in / gsz;
+  grouped_tile(lid, Mt, Nt, group_m, mt, nt);
 }
 
 // Source row (in units of K elements) of logical column J, or null past the
@@ -365,55 +371,36 @@ __device__ __forceinline__ uint4 pack8_bf16(const float* x) {
   return r;
 }
 
-template <int EPI, int TM, int TN, int MI>
-__device__ __forceinline__ void gemm_epilogue_lds(
-    const GemmParams& P,
-    typename std::conditional<MI == 32, floatx16_t, floatx4_t>::type (&acc)[TM / MI][TN / MI], int m0, int n0,
-    int wm, int wn, int lane, unsigned char* region) {
+template <int EPI, int TM, int TN>
+__device__ __forceinline__ void gemm_epilogue_lds(const GemmParams& P, floatx4_t (&acc)[TM / 16][TN / 16], int m0,
+                                                  int n0, int wm, int wn, int lane, unsigned char* region) {
   const int colbase = n0 + wn * TN;
   const int rowbase = m0 + wm * TM;
   // The accumulator elements of the wave tile's 32-row block ib, as (row in the
-  // block, column in the wave tile, value).  MI = 32: element v of subtile
-  // (ib, j) is row 8 (v/4) + 4 (lane/32) + v%4, column 32 j + lane%32.
-  // MI = 16: element v of subtile (2 ib + h, j) is row 16 h + 4 (lane/16) + v,
-  // column 16 j + lane%16.
+  // block, column in the wave tile, value): element v of subtile (2 ib + h, j) is
+  // row 16 h + 4 (lane/16) + v, column 16 j + lane%16.
   auto for_each_elem = [&](int ib, auto&& f) {
-    if constexpr (MI == 32) {
 #pragma unroll
-      for (int j = 0; j < TN / 32; ++j)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) f(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), j * 32 + (lane & 31), acc[ib][j][v]);
-    } else {
+      for (int j = 0; j < TN / 16; ++j)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int j = 0; j < TN / 16; ++j)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) f(16 * h + 4 * (lane >> 4) + v, j * 16 + (lane & 15), acc[2 * ib + h][j][v]);
-    }
+        for (int v = 0; v < 4; ++v) f(16 * h + 4 * (lane >> 4) + v, j * 16 + (lane & 15), acc[2 * ib + h][j][v]);
   };
   // The same for the pair epilogues, as (row, pair in the wave tile, first
   // half, second half): column c with c % 64 < 32 pairs with c + 32, pair
   // index 32 (c / 64) + c % 32.
   auto for_each_pair = [&](int ib, auto&& f) {
-    if constexpr (MI == 32) {
 #pragma unroll
-      for (int jp = 0; jp < TN / 64; ++jp)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          f(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), jp * 32 + (lane & 31), acc[ib][2 * jp][v], acc[ib][2 * jp + 1][v]);
-    } else {
+      for (int t = 0; t < TN / 64; ++t)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int t = 0; t < TN / 64; ++t)
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              f(16 * h + 4 * (lane >> 4) + v, t * 32 + u * 16 + (lane & 15), acc[2 * ib + h][4 * t + u][v],
-                acc[2 * ib + h][4 * t + u + 2][v]);
-    }
+          for (int v = 0; v < 4; ++v)
+            f(16 * h + 4 * (lane >> 4) + v, t * 32 + u * 16 + (lane & 15), acc[2 * ib + h][4 * t + u][v],
+              acc[2 * ib + h][4 * t + u + 2][v]);
   };
 #pragma unroll
   for (int ib = 0; ib < TM / 32; ++ib) {
@@ -550,16 +537,14 @@ __device__ __forceinline__ void gemm_epilogue_lds(
   }
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int STAGES, int BKT, int MI>
+template <int EPI, int BM, int BN, int WM, int WN, int STAGES, bool SPLIT>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_lds_kernel(GemmParams P) {
-  // MI: MFMA tile, 32 (v_mfma_f32_32x32x16_bf16) or 16 (v_mfma_f32_16x16x32_bf16:
-  // the same work per LDS byte in shorter, lower-power instructions)
-  static_assert(MI == 32 || MI == 16, "MFMA tile");
-  using acc_t = typename std::conditional<MI == 32, floatx16_t, floatx4_t>::type;
-  constexpr int KS = 512 / MI;  // k per MFMA: 16 or 32
+  // v_mfma_f32_16x16x32_bf16: the same work per LDS byte as 32x32x16 in shorter,
+  // lower-power instructions (a higher clock under load: 5-10% at 256x256)
+  constexpr int MI = 16, BKT = 64;
+  constexpr int KS = 512 / MI;  // k per MFMA
   constexpr int KK = BKT / KS;
-  static_assert(BKT == 32 || BKT == 64, "k-tile depth");
   static_assert(KK % 2 == 0, "the fragment double buffer alternates with the k-step: an even count per k-tile");
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN;
@@ -580,10 +565,23 @@ gemm_bf16_lds_kernel(GemmParams P) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int Mt = (P.M + BM - 1) / BM, Nt = (P.n_cnt + BN - 1) / BN;
-  int mt, nt;
-  tile_of(blockIdx.x, Mt, Nt, P.group_m, mt, nt);
-  const int m0 = mt * BM, n0 = P.n_off + nt * BN;
+  const int Mt = (P.M + BM - 1) / BM, Nt = (P.N + BN - 1) / BN;
+  // SPLIT: workgroup (split, tile) in one order, split by split, so that the tiles
+  // an XCD works on at a time share operands over the same part of K
+  int mt, nt, kt0 = 0, nk = P.K / BKT;
+  size_t slot = 0;
+  if constexpr (SPLIT) {
+    const int tiles = Mt * Nt, T = tiles * P.splits, q = T / 8, r = T % 8, x = blockIdx.x % 8;
+    const int lid = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + blockIdx.x / 8;
+    const int sp = lid / tiles, tile = lid - sp * tiles;
+    grouped_tile(tile, Mt, Nt, P.group_m, mt, nt);
+    kt0 = (int)((long long)nk * sp / P.splits);
+    nk = (int)((long long)nk * (sp + 1) / P.splits) - kt0;
+    slot = (size_t)sp * tiles + (size_t)nt * Mt + mt;
+  } else {
+    tile_of(blockIdx.x, Mt, Nt, P.group_m, mt, nt);
+  }
+  const int m0 = mt * BM, n0 = nt * BN;
 
   // per-lane sources of the direct-to-LDS loads (rows clamped; results of
   // clamped rows are never stored)
@@ -605,7 +603,7 @@ gemm_bf16_lds_kernel(GemmParams P) {
   }
   // load j (0 <= j < LI) of k-tile kt into its stage
   auto issue1 = [&](int kt, int j) {
-    const int k0 = kt * BKT;
+    const int k0 = (SPLIT ? kt0 + kt : kt) * BKT;
     bf16_t* st = S + (kt % STAGES) * STAGE;
     if (j < AI)
       __builtin_amdgcn_global_load_lds((const void*)(P.A + a_off[j] + k0),
@@ -615,13 +613,13 @@ gemm_bf16_lds_kernel(GemmParams P) {
                                        (lds_void_t*)(st + BM * BKT + (wave * BI + j - AI) * 64 * 8), 16, 0, 0);
   };
 
-  acc_t acc[FM][FN];
+  floatx4_t acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int v = 0; v < MI * MI / 64; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
   // an operand lane supplies row lr of its fragment, 16-byte k-chunk lk of the step
   const int lr = lane % MI, lk = lane / MI;
@@ -635,7 +633,6 @@ gemm_bf16_lds_kernel(GemmParams P) {
   };
   bf16x8_t fr[2][NF];
 
-  const int nk = P.K / BKT;
   const int npro = nk < STAGES ? nk : STAGES;
   for (int t = 0; t < npro; ++t)
 #pragma unroll
@@ -671,10 +668,7 @@ gemm_bf16_lds_kernel(GemmParams P) {
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          if constexpr (MI == 32)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[cur][i], fr[cur][FM + j], acc[i][j], 0, 0, 0);
-          else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[cur][i], fr[cur][FM + j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[cur][i], fr[cur][FM + j], acc[i][j], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
           if (more && m < NF) fr[nxt][m] = *(const bf16x8_t*)(na + foff[m]);
           if (kk == KK - 1 && refill) {
@@ -689,14 +683,46 @@ gemm_bf16_lds_kernel(GemmParams P) {
         if (more) fr[nxt][g] = *(const bf16x8_t*)(na + foff[g]);
     }
   }
-  const bool fast = EPI == EPI_RESID ? (P.N % 8) == 0
-                                     : (P.npairs % 8) == 0 && (EPI == EPI_SWIGLU || (P.dh % 16) == 0);
-  if (fast) {
-    barrier_lds();  // every wave is done with the stages
-    gemm_epilogue_lds<EPI, TM, TN, MI>(P, acc, m0, n0, wm, wn, lane, smem + wave * epi_region_bytes<EPI, TN>());
-  } else if constexpr (MI == 32) {
-    gemm_epilogue_t<EPI, TM, TN, FM, FN>(P, acc, m0, n0, wm, wn, lr, lk);
-  }  // (the launch takes MI = 16 only for the shapes of the staged epilogue)
+  if constexpr (SPLIT) {
+    float* o = P.part + slot * (BM * BN) + (size_t)(wave * FM * FN) * (MI * MI) + lane * 4;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) *(floatx4_t*)(o + (i * FN + j) * (MI * MI)) = acc[i][j];
+    return;
+  }
+  barrier_lds();  // every wave is done with the stages
+  gemm_epilogue_lds<EPI, TM, TN>(P, acc, m0, n0, wm, wn, lane, smem + wave * epi_region_bytes<EPI, TN>());
+}
+
+// The splits' accumulators of a tile added in order, and the epilogue; the layout
+// is that of gemm_bf16_lds_kernel with the same template arguments.
+template <int EPI, int BM, int BN, int WM, int WN>
+__global__ void __launch_bounds__(WM * WN * 64) gemm_finish_kernel(GemmParams P) {
+  constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int Mt = (P.M + BM - 1) / BM, tiles = gridDim.x;
+  const int mt = blockIdx.x % Mt, nt = blockIdx.x / Mt;
+  floatx4_t acc[FM][FN];
+  const float* o = P.part + (size_t)blockIdx.x * (BM * BN) + (size_t)(wave * FM * FN) * 256 + lane * 4;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = *(const floatx4_t*)(o + (i * FN + j) * 256);
+  for (int sp = 1; sp < P.splits; ++sp) {
+    o += (size_t)tiles * (BM * BN);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const floatx4_t p = *(const floatx4_t*)(o + (i * FN + j) * 256);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][j][v] += p[v];
+      }
+  }
+  gemm_epilogue_lds<EPI, TM, TN>(P, acc, mt * BM, nt * BN, wave / WN, wave % WN, lane,
+                                     smem + wave * epi_region_bytes<EPI, TN>());
 }
 
 // ---- fp32 path ------------------------------------------------------------------
@@ -865,30 +891,95 @@ static hipError_t run_bf16(const GemmParams& P, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int STAGES, int BKT, int MI>
+template <int EPI, int BM, int BN, int WM, int WN, int STAGES, bool SPLIT>
 static hipError_t run_lds_t(const GemmParams& P, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
-  const int tiles = ((P.M + BM - 1) / BM) * ((P.n_cnt + BN - 1) / BN);
-  const size_t lds = (size_t)STAGES * (BM + BN) * BKT * sizeof(bf16_t);
+  const int tiles = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
+  const size_t lds = (size_t)STAGES * (BM + BN) * 64 * sizeof(bf16_t);
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute((const void*)gemm_bf16_lds_kernel<EPI, BM, BN, WM, WN, STAGES, BKT, MI>,
+    (void)hipFuncSetAttribute((const void*)gemm_bf16_lds_kernel<EPI, BM, BN, WM, WN, STAGES, SPLIT>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if constexpr (SPLIT)
+      (void)hipFuncSetAttribute((const void*)gemm_finish_kernel<EPI, BM, BN, WM, WN>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                WM * WN * epi_region_bytes<EPI, BN / WN>());
     attr = true;
   }
-  return launch_ext(gemm_bf16_lds_kernel<EPI, BM, BN, WM, WN, STAGES, BKT, MI>, dim3(tiles), dim3(NT),
-                    (uint32_t)lds, s, P);
+  if constexpr (SPLIT) {
+    g_launch_events = LaunchEvents{nullptr, nullptr, 0};  // two launches: timed around both
+    gemm_bf16_lds_kernel<EPI, BM, BN, WM, WN, STAGES, true><<<tiles * P.splits, NT, lds, s>>>(P);
+    gemm_finish_kernel<EPI, BM, BN, WM, WN>
+        <<<tiles, NT, WM * WN * epi_region_bytes<EPI, BN / WN>(), s>>>(P);
+    return hipGetLastError();
+  } else {
+    return launch_ext(gemm_bf16_lds_kernel<EPI, BM, BN, WM, WN, STAGES, false>, dim3(tiles), dim3(NT),
+                      (uint32_t)lds, s, P);
+  }
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int BKT = 64, int MI = 32>
+template <int BM, int BN, int WM, int WN, int STAGES>
 static hipError_t run_lds(const GemmParams& P, hipStream_t s) {
-  if (P.epi == EPI_RESID) return run_lds_t<EPI_RESID, BM, BN, WM, WN, STAGES, BKT, MI>(P, s);
-  if (P.epi == EPI_SWIGLU) return run_lds_t<EPI_SWIGLU, BM, BN, WM, WN, STAGES, BKT, MI>(P, s);
-  return run_lds_t<EPI_QKV_ROPE, BM, BN, WM, WN, STAGES, BKT, MI>(P, s);
+  if (P.splits > 1) {
+    if (P.epi == EPI_RESID) return run_lds_t<EPI_RESID, BM, BN, WM, WN, STAGES, true>(P, s);
+    if (P.epi == EPI_SWIGLU) return run_lds_t<EPI_SWIGLU, BM, BN, WM, WN, STAGES, true>(P, s);
+    return run_lds_t<EPI_QKV_ROPE, BM, BN, WM, WN, STAGES, true>(P, s);
+  }
+  if (P.epi == EPI_RESID) return run_lds_t<EPI_RESID, BM, BN, WM, WN, STAGES, false>(P, s);
+  if (P.epi == EPI_SWIGLU) return run_lds_t<EPI_SWIGLU, BM, BN, WM, WN, STAGES, false>(P, s);
+  return run_lds_t<EPI_QKV_ROPE, BM, BN, WM, WN, STAGES, false>(P, s);
 }
-// the shapes of the LDS-staged epilogue (8 consecutive outputs per lane)
-static bool staged_epilogue_shape(const GemmParams& P) {
-  return P.epi == EPI_RESID ? (P.N % 8) == 0 : (P.npairs % 8) == 0 && (P.epi == EPI_SWIGLU || (P.dh % 16) == 0);
+
+// the shapes of the LDS kernel: whole 64-deep k-tiles and the staged epilogue
+// (8 consecutive outputs per lane)
+static bool lds_shape(int epi, int K, int nlog, int npairs, int dh) {
+  if (K % 64 != 0) return false;
+  return epi == EPI_RESID ? nlog % 8 == 0 : npairs % 8 == 0 && (epi == EPI_SWIGLU || dh % 16 == 0);
+}
+
+// Tile and K split of a product.  One workgroup runs on a compute unit at a
+// time, so a launch takes ceil(tiles * splits / 256) rounds, each of K / splits
+// steps whose time depends on the tile alone (ns per k with every unit busy,
+// measured at M = 300 .. 3000, K = 3584 .. 18944: 256x256 25.5, 128x256 15.0,
+// 256x128 14.7, 128x128 9.8: the larger the tile, the fewer operand bytes per
+// product).  Splits add a launch and their sums' way through memory (8 us, and
+// 8 bytes per sum at 3.7 TB/s).  The plan with the least of that, in us under the
+// profiler: 600 x 12288 x 4096 113 -> 78 (240 tiles of 128x256, not 144 of
+// 256x256), 600 x 4096 x 11008 119 -> 83 (80 tiles in 3 parts, not 160 whole ones
+// of 128x128), 3001 x 37888 x 3584 930 -> 788 (7 rounds of 256x256, not one of
+// them and 12 of 256x128), 3001 x 3584 x 18944 664 -> 454 (168 tiles in 3 parts).
+struct GemmPlan {
+  int tile, splits;
+  size_t bytes;  // scratch of the splits' sums
+};
+static GemmPlan gemm_plan(int M, int nlog, int K, bool may_split) {
+  static const struct {
+    int bm, bn;
+    double ns;
+  } T[4] = {{256, 256, 25.5}, {128, 256, 15.0}, {256, 128, 14.7}, {128, 128, 9.8}};
+  GemmPlan best = {0, 1, 0};
+  double cost = 0.0;
+  for (int t = 0; t < 4; ++t) {
+    const long long tiles = (long long)cdiv(M, T[t].bm) * cdiv(nlog, T[t].bn);
+    for (int sp = 1; sp <= 8; ++sp) {
+      if (sp > 1 && (!may_split || K / 64 < 8 * sp || tiles > 512)) break;
+      const size_t bytes = sp > 1 ? (size_t)tiles * sp * T[t].bm * T[t].bn * sizeof(float) : 0;
+      const double c = (double)((tiles * sp + 255) / 256) * K / sp * T[t].ns * 1e-3 +
+                       (sp > 1 ? 8.0 + 2.0 * (double)bytes / 3.7e6 : 0.0);
+      if ((t == 0 && sp == 1) || c < cost) {
+        cost = c;
+        best = {t, sp, bytes};
+      }
+    }
+  }
+  return best;
+}
+
+size_t gemm_scratch_bytes(int dtype, const GemmArgs& g) {
+  if (dtype != SAS_BF16 || g.M <= 0) return 0;
+  const int npairs = g.epi == EPI_SWIGLU ? g.N : (g.epi == EPI_QKV_ROPE ? g.N / 2 : 0);
+  const int nlog = g.epi == EPI_RESID ? g.N : (npairs + 31) / 32 * 64;
+  return lds_shape(g.epi, g.K, nlog, npairs, g.head_dim) ? gemm_plan(g.M, nlog, g.K, true).bytes : 0;
 }
 
 static bool attrs_done = false;
@@ -947,8 +1038,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   // tile order: groups of 8 M tiles; the long-K residual product (the MLP's
   // down projection, K > 2N) runs faster with groups of 2 (measured 4-5%)
   P.group_m = (g.epi == EPI_RESID && g.K > 2 * nlog) ? 2 : 8;
-  P.n_off = 0;
-  P.n_cnt = nlog;
+  P.splits = 1;
+  P.part = g.part;
   P.seq_len = g.seq_len;
   P.rope = g.rope;
   P.row_pos = g.row_pos;
@@ -959,37 +1050,16 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
                            : PageGeom{nullptr, 0, 1, 0};
   const long big_tiles = (long)((g.M + 255) / 256) * ((nlog + 255) / 256);
   if (g.epi == EPI_F32OUT) return hipErrorInvalidValue;  // bf16 fp32-output products go through gemv
-  if (g.K % 64 == 0) {
-    // Tile choice from measurements on MI355X with the weights streamed
-    // from HBM, as in a layer (grouped, XCD-aware tile order).  Long M:
-    // 256x256 tiles.  Short M: 256x256 tiles where they fill the
-    // CUs; when they would take a second, partly empty round, one full
-    // round of 256x256 tiles followed by 256x128 tiles for the remaining
-    // columns; narrow products (N < 8192) with 128x128 tiles.
-    // The 16x16x32 MFMA (same LDS traffic per flop, lower power, so a higher
-    // clock under load) where the staged epilogue takes the shape: 5-10%
-    // faster at 256x256 and 256x128, no gain at 128x128.
-    const bool mi16 = staged_epilogue_shape(P);
-    auto big = [&](const GemmParams& Q) {
-      return mi16 ? run_lds<256, 256, 2, 4, 2, 64, 16>(Q, s) : run_lds<256, 256, 2, 4, 2>(Q, s);
-    };
-    if (g.M >= 4096) return big(P);
-    if (nlog >= 8192) {
-      const int mt = (g.M + 255) / 256, nt = (nlog + 255) / 256;
-      const int full = 256 / mt;  // 256-column tiles per full round
-      if ((long)mt * nt > 256 && full > 0) {
-        g_launch_events = LaunchEvents{nullptr, nullptr, 0};  // two launches: timed around both
-        GemmParams P1 = P, P2 = P;
-        P1.n_cnt = full * 256;
-        P2.n_off = full * 256;
-        P2.n_cnt = nlog - full * 256;
-        hipError_t e = big(P1);
-        if (e != hipSuccess) return e;
-        return mi16 ? run_lds<256, 128, 4, 2, 3, 64, 16>(P2, s) : run_lds<256, 128, 4, 2, 3>(P2, s);
-      }
-      return big(P);
+  if (lds_shape(g.epi, g.K, nlog, npairs, g.head_dim)) {
+    GemmPlan plan = gemm_plan(g.M, nlog, g.K, g.part != nullptr);
+    if (plan.bytes > g.part_bytes) plan = gemm_plan(g.M, nlog, g.K, false);
+    P.splits = plan.splits;
+    switch (plan.tile) {
+      case 0: return run_lds<256, 256, 2, 4, 2>(P, s);
+      case 1: return run_lds<128, 256, 2, 4, 3>(P, s);
+      case 2: return run_lds<256, 128, 4, 2, 3>(P, s);
+      default: return run_lds<128, 128, 4, 2, 4>(P, s);
     }
-    return run_lds<128, 128, 4, 2, 4>(P, s);
   }
   if (big_tiles >= 256) return run_bf16<256, 256, 2, 4>(P, s);
   return run_bf16<128, 128, 2, 2>(P, s);

@@ -86,7 +86,13 @@ struct GemmArgs {
   // into the paged cache, row r being position r % seq_len of sequence
   // r / seq_len (only where gemm_fills_cache holds), or NULL
   const struct DecodeArgs* prefill_cache;
+  // launch_gemm: scratch for products whose K is split over workgroups
+  // (gemm_scratch_bytes; NULL: not split)
+  float* part;
+  size_t part_bytes;
 };
+// Scratch that the product wants (0: it is not split).  Reads epi, M, N, K, head_dim.
+size_t gemm_scratch_bytes(int dtype, const GemmArgs& a);
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // Does launch_gemm write the K/V pages of `a.prefill_cache` itself (the bf16
 // staged QKV epilogue)?  Otherwise the caller fills the cache.
