@@ -688,7 +688,7 @@ __global__ void __launch_bounds__(1024) bwd_jobs_kernel(const int* __restrict__ 
   const int T = Z * ntiles, tid = threadIdx.x;
   const int per = (T + 1023) / 1024, lo = min(T, tid * per), hi = min(T, lo + per);
   auto parts_of = [&](int c) {  // parts of a tile of c rows
-    const int ch = (c + 31) / 32;
+    const int ch = (c + 63) / 64;  // chunks of the dK/dV pass
     return ch > chunks ? (ch + chunks - 1) / chunks : 1;
   };
   int s_row = 0, s_job = 0, s_slot = 0;
@@ -741,54 +741,73 @@ __global__ void __launch_bounds__(256) bwd_dkv_sum_kernel(const int2* __restrict
   }
 }
 
+// LDS tiles of the dK/dV pass: rows of DH values without padding, the 16-byte
+// chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
+// (the row-major operand reads) then lie in distinct banks, and so do the four
+// rows x 32 dimensions that half a wave takes with a transposing read.
+template <int DH>
+__device__ __forceinline__ int lds_swz(int r) {
+  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+template <int DH>
+__device__ __forceinline__ int lds_chunk(int r, int c) { return r * DH + ((c ^ lds_swz<DH>(r)) << 3); }
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+// ds_read_b64_tr_b16: in each group of 16 lanes, lane 4 j + a names 4 consecutive
+// values of row j of a 4 x 16 tile, and lane i receives column i (rows 0..3).
+__device__ __forceinline__ uint2 lds_read_tr(const unsigned char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p));
+}
+
 // Pass 2 (dK, dV): one workgroup of 4 waves per 64 keys of one (batch, KV
-// group); a pair of waves owns 32 keys and splits the head dimension: each
-// wave holds its half of the keys' K and V as the B operands of the partial
-// products S = Q K^T and dP = dO V^T over its dimensions (lane = key, 16 rows
-// per lane) and accumulates dK and dV for its dimensions only; the two
-// partial products are exchanged through LDS and added (the same sum in both
-// waves), which keeps a wave within 256 registers (two waves per SIMD).  The rows are those of the tile's list (selections), or, when
-// every earlier block is attended (DENSE, full scope), the consecutive rows
-// from the tile on, in chunks of 32 that reach the tile.  Work items are
-// (chunk, head of the group); the row indices of the next chunk are read one
-// chunk ahead, and the Q and dO rows of the next item are loaded into
-// registers while the current one is multiplied, then written to LDS both
-// row-major (A of S and dP) and transposed (A of dK^T += Q^T dS and
-// dV^T += dO^T P, read in the accumulator's row permutation).  P and dS stay
-// in registers; the causal mask compares each key with its row's index.
+// group).  The rows are those of the tile's list (selections), or, when every
+// earlier block is attended (DENSE, full scope), the consecutive rows from the
+// tile on, in chunks of 64 that reach the tile; work items are (chunk, head of
+// the group).  Wave (kh, rh) multiplies 32 of the chunk's rows by 32 of the keys
+// and accumulates dK and dV of its keys over its rows, all dimensions (128
+// registers); the two row halves are added through LDS once per job.  Bound by
+// LDS bandwidth and matrix cores: K and V stay in LDS for the job, the chunk's Q
+// and dO rows are staged once, row-major, and read both as rows (A of S = Q K^T
+// and dP = dO V^T) and, with the transposing read, as columns (A of dK^T += Q^T dS
+// and dV^T += dO^T P, in the accumulator's row permutation): 48 KB of reads per
+// wave and 32 x 32 block, 64 KB of LDS per workgroup, two workgroups per compute
+// unit.  P and dS never leave registers.  4 x 4096 tokens, 32/32 heads, K = 16:
+// 1.04 ms; waves that split the dimensions, exchanged partial S and dP
+// through LDS and staged transposed copies took 1.64 ms.
+// The next item's rows are loaded into registers while this one is multiplied;
+// row indices are read one chunk ahead.
+constexpr int DKV_ROWS = 64;
 template <int DH, bool PLAIN>
 __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int ktile, const int g, const int bi,
                                                  const int part, const int parts, const int slot) {
-  constexpr int NTH = 256, KT = 64;
-  constexpr int KP = DH + 8;
-  constexpr int QP = 32 + 4;
-  constexpr int C8 = DH / 8;            // 16-byte pieces of a row
-  constexpr int QPT = 32 * C8 / NTH;    // chunk rows staged per thread (2 or 1)
-  constexpr int DHH = DH / 2;           // dimensions of a wave
-  __shared__ __align__(16) bf16_t Qs[32 * KP];
-  __shared__ __align__(16) bf16_t Ds[32 * KP];
-  __shared__ __align__(16) bf16_t Qt[DH * QP];
-  __shared__ __align__(16) bf16_t Dt[DH * QP];
-  __shared__ __align__(16) float delta_s[32];
-  __shared__ __align__(16) int trow_s[32];      // row index of each staged row (n: none)
-  __shared__ __align__(16) float off_s[4][32];  // log2-domain bias - LSE per (sub-block, row); -inf: not attended
-  __shared__ __align__(16) float wt_s[4][32];   // value weight per (sub-block, row) (outer gate)
-  __shared__ uint32_t flags[BWD_MAX_SEQ / 32 / 32];
-  __shared__ __align__(16) float xs[4][2][16][64];  // each wave's partial S and dP
+  constexpr int KT = 64, RC = DKV_ROWS;
+  constexpr int C8 = DH / 8;              // 16-byte pieces of a row
+  constexpr int NR = RC * C8 / 256;       // chunk rows staged per thread
+  constexpr int RS = 256 / C8;            // ... this many rows apart
+  __shared__ __align__(16) bf16_t tiles[4 * 64 * DH];  // Q, dO, K, V; at the end the row halves' sums
+  bf16_t* const Qs = tiles;
+  bf16_t* const Ds = tiles + 64 * DH;
+  bf16_t* const Ks = tiles + 2 * 64 * DH;
+  bf16_t* const Vs = tiles + 3 * 64 * DH;
+  __shared__ __align__(16) float delta_s[RC];
+  __shared__ __align__(16) int rows_s[2][RC];   // row index of each staged row (n: none), by chunk parity
+  __shared__ __align__(16) float off_s[4][RC];  // log2-domain bias - LSE per (sub-block, row); -inf: not attended
+  __shared__ __align__(16) float wt_s[PLAIN ? 1 : 4][RC];  // value weight per (sub-block, row) (outer gate)
+  __shared__ uint32_t flags[BWD_MAX_SEQ / RC / 32];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lk = lane >> 5;
-  const int kh = wave >> 1, dhf = wave & 1;  // key half, dimension half
+  const int kh = wave >> 1, rh = wave & 1;  // key half, row half
   const int k0 = ktile * KT;
   const int n = P.n, B = P.B, H = P.H, G = H / P.Hkv;
   const int key = k0 + kh * 32 + lr;
-  const bool kvalid = key < n;
   const int bshift = 31 - __clz(B < 64 ? B : 64);
   const int nsb = KT >> bshift;  // sub-blocks of min(B, 64) keys in the tile: 1, 2 or 4
   const int m_hi = min(n - 1, k0 + KT - 1) / B;
   const int NB = (n + B - 1) / B;
   const int NW = (NB + 31) / 32;
-  const int nqc = (n + 31) / 32;
+  const int nqc = (n + RC - 1) / RC;
   const bool dense = P.mode == SAS_MODE_DENSE, gated = P.mode == SAS_MODE_GATED;
   const bool ste = gated && P.ste, outer = gated && P.outer;
   const bool fullatt = gated && P.full && !P.ste;  // every historical block attended, gates from the table
@@ -798,95 +817,76 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
   int lbase = 0, lcnt = 0;
   if (use_list) {  // this part of the tile's list: whole chunks
     const size_t tile = ((size_t)bi * P.Hkv + g) * ntk + ktile;
-    const int cnt = P.tile_cnt[tile], ch = (cnt + 31) / 32, cp = (ch + parts - 1) / parts;
-    const int lo = min(cnt, part * cp * 32);
+    const int cnt = P.tile_cnt[tile], ch = (cnt + RC - 1) / RC, cp = (ch + parts - 1) / parts;
+    const int lo = min(cnt, part * cp * RC);
     lbase = P.tile_off[tile] + lo;
-    lcnt = min(cnt - lo, cp * 32);
+    lcnt = min(cnt - lo, cp * RC);
   }
-  const int nchunk = use_list ? (lcnt + 31) / 32 : nqc;
+  const int nchunk = use_list ? (lcnt + RC - 1) / RC : nqc;
 
+  // the previous job of this workgroup is done with LDS
+  __syncthreads();
+  const int c8 = tid % C8, sr = tid / C8;  // staging role: rows sr + RS i, 16-byte piece c8
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int kr = sr + RS * i;
+    const size_t off = (((size_t)bi * n + min(k0 + kr, n - 1)) * P.Hkv + g) * DH + c8 * 8;
+    uint4 kv = *(const uint4*)((const bf16_t*)P.Kt + off), vv = *(const uint4*)((const bf16_t*)P.V + off);
+    if (k0 + kr >= n) kv = vv = make_uint4(0, 0, 0, 0);
+    *(uint4*)(Ks + lds_chunk<DH>(kr, c8)) = kv;
+    *(uint4*)(Vs + lds_chunk<DH>(kr, c8)) = vv;
+  }
   // without a list: the chunks that reach the tile (their rows lie in its blocks, or,
   // every earlier block being attended, their earliest row's document starts in time)
-  const int qc0 = use_list ? 0 : k0 / 32;
+  const int qc0 = use_list ? 0 : k0 / RC;
   if (!use_list) {
-    for (int w = tid; w < (nqc + 31) / 32; w += NTH) flags[w] = 0;
+    for (int w = tid; w < (nqc + 31) / 32; w += 256) flags[w] = 0;
     __syncthreads();
-    for (int qc = qc0 + tid; qc < nqc; qc += NTH) {
-      const bool any = ((dense || fullatt) && doc_first(P.doc, bi, NB, qc * 32, B) <= m_hi) || (qc * 32) / B <= m_hi;
+    for (int qc = qc0 + tid; qc < nqc; qc += 256) {
+      const bool any = ((dense || fullatt) && doc_first(P.doc, bi, NB, qc * RC, B) <= m_hi) || (qc * RC) / B <= m_hi;
       if (any) atomicOr(&flags[qc >> 5], 1u << (qc & 31));
     }
     __syncthreads();
   }
   auto next_chunk = [&](int c) { return use_list ? c : next_set(flags, c, nqc); };
+  // row index of staged row r of chunk c (n: none)
+  auto row_of = [&](int c, int r) -> int {
+    if (c >= nchunk) return n;
+    const int i = c * RC + r;
+    if (use_list) return i < lcnt ? P.tile_rows[lbase + i] : n;
+    return min(i, n);
+  };
 
-  bf16x8_t kb[DHH / 16], vb[DHH / 16];
-  {
-    const size_t off = (((size_t)bi * n + (kvalid ? key : 0)) * P.Hkv + g) * DH + dhf * DHH;
+  floatx16_t dk[DH / 32], dv[DH / 32];
 #pragma unroll
-    for (int ks = 0; ks < DHH / 16; ++ks) {
-      uint4 u = kvalid ? *(const uint4*)((const bf16_t*)P.Kt + off + ks * 16 + lk * 8) : make_uint4(0, 0, 0, 0);
-      kb[ks] = *(bf16x8_t*)&u;
-      uint4 w = kvalid ? *(const uint4*)((const bf16_t*)P.V + off + ks * 16 + lk * 8) : make_uint4(0, 0, 0, 0);
-      vb[ks] = *(bf16x8_t*)&w;
-    }
-  }
-  floatx16_t dk[DHH / 32], dv[DHH / 32];
-#pragma unroll
-  for (int dt = 0; dt < DHH / 32; ++dt)
+  for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       dk[dt][v] = 0.f;
       dv[dt][v] = 0.f;
     }
   const float qk_scale = P.sm_scale * BLOG2E;
-
-  // staging roles: rows qg * QPT + i, 16-byte piece c8; row index / delta row bq (tid < 32);
-  // bias (row bq, sub-block bsb)
-  const int c8 = tid % C8, qg = tid / C8;
-  const int bq = tid & 31, bsb = tid >> 5;
-  // row index of staged row r of chunk c (n: none)
-  auto row_of = [&](int c, int r) -> int {
-    if (use_list) {
-      const int i = c * 32 + r;
-      return i < lcnt ? P.tile_rows[lbase + i] : n;
-    }
-    const int t = c * 32 + r;
-    return t < n ? t : n;
-  };
-  // row indices of the chunk being loaded (rt, bt) and of the chunk after it (rt_n, bt_n)
-  int rt[QPT], rt_n[QPT], bt = n, bt_n = n;
-  uint4 rq[QPT], rd[QPT];
+  const int bq = tid & 63, bsb = wave;  // row scalars: row bq; its bias in sub-block bsb
+  uint4 rq[NR], rd[NR];
   float r_lse = 0.f, r_delta = 0.f, r_lg = 0.f;
   uint32_t r_mw = 0;
   int r_fb = 0;  // first block of the row's document
-  int pc = -1;   // chunk whose row indices are in rt
-
-  auto load_rows = [&](int c, int* dst, int& b) {
-#pragma unroll
-    for (int i = 0; i < QPT; ++i) dst[i] = c < nchunk ? row_of(c, qg * QPT + i) : n;
-    b = c < nchunk ? row_of(c, bq) : n;
-  };
-  auto prefetch = [&](int qc, int hg) {
-    if (qc != pc) {  // a new chunk: its rows were read one chunk ahead
-#pragma unroll
-      for (int i = 0; i < QPT; ++i) rt[i] = rt_n[i];
-      bt = bt_n;
-      pc = qc;
-      load_rows(next_chunk(qc + 1), rt_n, bt_n);
-    }
+  auto prefetch = [&](int par, int hg) {
     const int h = g * G + hg;
 #pragma unroll
-    for (int i = 0; i < QPT; ++i) {
-      const int t = rt[i];
-      const size_t off = (((size_t)bi * n + t) * H + h) * DH + c8 * 8;
-      rq[i] = t < n ? *(const uint4*)((const bf16_t*)P.Q + off) : make_uint4(0, 0, 0, 0);
-      rd[i] = t < n ? *(const uint4*)((const bf16_t*)P.dO + off) : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < NR; ++i) {
+      const int t = rows_s[par][sr + RS * i];
+      const size_t off = (((size_t)bi * n + min(t, n - 1)) * H + h) * DH + c8 * 8;
+      rq[i] = *(const uint4*)((const bf16_t*)P.Q + off);
+      rd[i] = *(const uint4*)((const bf16_t*)P.dO + off);
+      if (t >= n) rq[i] = rd[i] = make_uint4(0, 0, 0, 0);
     }
-    const int t = bt;
-    if (tid < 32) r_delta = t < n ? P.delta[((size_t)bi * H + h) * n + t] : 0.f;
+    const int t = rows_s[par][bq];
+    const size_t hr = ((size_t)bi * H + h) * n + min(t, n - 1);
+    if (wave == 0) r_delta = t < n ? P.delta[hr] : 0.f;
     if (bsb < nsb) {
       const int kstart = k0 + (bsb << bshift), m = kstart / B;
-      r_lse = t < n ? P.lse[((size_t)bi * H + h) * n + t] : 0.f;
+      r_lse = t < n ? P.lse[hr] : 0.f;
       r_fb = t < n ? doc_first(P.doc, bi, NB, t, B) : 0;
       r_mw = 0u;
       r_lg = 0.f;
@@ -896,38 +896,15 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
       }
     }
   };
-  auto commit = [&]() {
+  auto commit = [&](int par) {
 #pragma unroll
-    for (int i = 0; i < QPT; ++i) {
-      *(uint4*)(Qs + (qg * QPT + i) * KP + c8 * 8) = rq[i];
-      *(uint4*)(Ds + (qg * QPT + i) * KP + c8 * 8) = rd[i];
+    for (int i = 0; i < NR; ++i) {
+      *(uint4*)(Qs + lds_chunk<DH>(sr + RS * i, c8)) = rq[i];
+      *(uint4*)(Ds + lds_chunk<DH>(sr + RS * i, c8)) = rd[i];
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int sh = (e & 1) * 16;
-      const int wd = e >> 1;
-      uint32_t x[QPT], y[QPT];
-#pragma unroll
-      for (int i = 0; i < QPT; ++i) {
-        x[i] = (((const uint32_t*)&rq[i])[wd] >> sh) & 0xffffu;
-        y[i] = (((const uint32_t*)&rd[i])[wd] >> sh) & 0xffffu;
-      }
-      bf16_t* qd = Qt + (c8 * 8 + e) * QP + qg * QPT;
-      bf16_t* dd = Dt + (c8 * 8 + e) * QP + qg * QPT;
-      if constexpr (QPT == 2) {
-        *(uint32_t*)qd = x[0] | (x[1] << 16);
-        *(uint32_t*)dd = y[0] | (y[1] << 16);
-      } else {
-        *(uint16_t*)qd = (uint16_t)x[0];
-        *(uint16_t*)dd = (uint16_t)y[0];
-      }
-    }
-    if (tid < 32) {
-      delta_s[tid] = r_delta;
-      trow_s[tid] = bt;
-    }
+    if (wave == 0) delta_s[bq] = r_delta;
     if (bsb < nsb) {
-      const int t = bt, kstart = k0 + (bsb << bshift), m = kstart / B;
+      const int t = rows_s[par][bq], kstart = k0 + (bsb << bshift), m = kstart / B;
       float bb = -INFINITY, w = 1.f;
       if (t < n && kstart <= t) {
         if (m == t / B || (dense && m >= r_fb)) {
@@ -939,139 +916,165 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
         }
       }
       off_s[bsb][bq] = bb - r_lse * BLOG2E;
-      wt_s[bsb][bq] = w;
+      if constexpr (!PLAIN) wt_s[bsb][bq] = w;
     }
   };
 
-  int qc = next_chunk(qc0), hg = 0;
-  load_rows(qc, rt_n, bt_n);
-  if (qc < nchunk) prefetch(qc, 0);
-  while (qc < nchunk) {
-    commit();
-    lds_barrier();
-    int nq = qc, nh = hg + 1;
-    if (nh == G) {
-      nh = 0;
-      nq = next_chunk(qc + 1);
-    }
-    if (nq < nchunk) prefetch(nq, nh);
+  // byte offsets of this lane's operands in a tile; a step or dimension block is an
+  // exclusive-or of the chunk bits.  Rows: row rh 32 + lr of Q / dO and kh 32 + lr of
+  // K / V, chunk 2 ks + lk.  Columns (transposing read): dimensions 32 dt + 16 (lane
+  // / 16 % 2) + 4 (lane % 4) .. of row 4 lk + 8 half + (lane % 16) / 4 of the wave's rows.
+  uint32_t o_row = (rh * 32 + lr) * DH * 2 + ((lk ^ lds_swz<DH>(lr)) << 4);
+  uint32_t o_key = (kh * 32 + lr) * DH * 2 + ((lk ^ lds_swz<DH>(lr)) << 4);
+  uint32_t o_tr[2];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    const int r = 4 * lk + 8 * hf + ((lane & 15) >> 2);
+    o_tr[hf] = (rh * 32 + r) * DH * 2 + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ lds_swz<DH>(r)) << 4) +
+               (lane & 1) * 8;
+  }
+  const unsigned char* const tb = (const unsigned char*)tiles;
+  constexpr int TB = 64 * DH * 2;  // bytes of a tile
 
-    floatx16_t sc, dp;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      sc[v] = 0.f;
-      dp[v] = 0.f;
-    }
-#pragma unroll
-    for (int ks = 0; ks < DHH / 16; ++ks) {
-      const bf16x8_t aq = *(const bf16x8_t*)(Qs + lr * KP + dhf * DHH + ks * 16 + lk * 8);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, kb[ks], sc, 0, 0, 0);
-      const bf16x8_t ad = *(const bf16x8_t*)(Ds + lr * KP + dhf * DHH + ks * 16 + lk * 8);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, vb[ks], dp, 0, 0, 0);
-    }
-    // the pair's partial products: written, exchanged, added (commutative, the same in both)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      xs[wave][0][v][lane] = sc[v];
-      xs[wave][1][v][lane] = dp[v];
-    }
+  int qc = next_chunk(qc0), hg = 0, par = 0;
+  int nqcx = qc < nchunk ? next_chunk(qc + 1) : nchunk;  // the chunk after qc
+  int r_next = n;                                        // its row of this thread (wave 0)
+  if (wave == 0) {
+    rows_s[0][bq] = row_of(qc, bq);
+    r_next = row_of(nqcx, bq);
+  }
+  __syncthreads();
+  if (qc < nchunk) prefetch(0, 0);
+  while (qc < nchunk) {
+    commit(par);
+    if (hg == 0 && wave == 0) rows_s[par ^ 1][bq] = r_next;
     lds_barrier();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      sc[v] += xs[wave ^ 1][0][v][lane];
-      dp[v] += xs[wave ^ 1][1][v][lane];
+    const bool last_head = hg + 1 == G;
+    int after = nchunk;
+    if (last_head) {
+      after = nqcx < nchunk ? next_chunk(nqcx + 1) : nchunk;
+      if (nqcx < nchunk) prefetch(par ^ 1, 0);
+      if (wave == 0) r_next = row_of(after, bq);
+    } else {
+      prefetch(par, hg + 1);
     }
-    // lane: key column `key`; staged rows 8 j + 4 lk + i (v = 4 j + i)
-    const int sbk = (kh * 32 + lr) >> bshift;
-    const bool diag = trow_s[0] < k0 + KT - 1;  // some row precedes a key of the tile: mask key > row
-    // dV^T += dO^T P and dK^T += Q^T dS, 16 rows per step in the accumulator's row permutation;
-    // each step's P and dS are formed and packed just before its MFMAs
+
+    // (the operand addresses are formed anew for each item: kept, they would spill)
+    asm volatile("" : "+v"(o_row), "+v"(o_key), "+v"(o_tr[0]), "+v"(o_tr[1]));
+    const int* trow = rows_s[par] + rh * 32;
+    if (trow[0] < n) {  // rows ascend: else this wave's half holds none
+      floatx16_t sc, dp;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      float pv[8], sv[8];
+      for (int v = 0; v < 16; ++v) {
+        sc[v] = 0.f;
+        dp[v] = 0.f;
+      }
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * ks + jj;
-        const float4 of = *(const float4*)&off_s[sbk][8 * j + 4 * lk];
-        const float4 de = *(const float4*)&delta_s[8 * j + 4 * lk];
-        const int4 tr = *(const int4*)&trow_s[8 * j + 4 * lk];
-        float4 wt = make_float4(1.f, 1.f, 1.f, 1.f);
-        if (!PLAIN && outer) wt = *(const float4*)&wt_s[sbk][8 * j + 4 * lk];
-        const float ofv[4] = {of.x, of.y, of.z, of.w}, dev[4] = {de.x, de.y, de.z, de.w};
-        const float wv[4] = {wt.x, wt.y, wt.z, wt.w};
-        const int trv[4] = {tr.x, tr.y, tr.z, tr.w};
+      for (int ks = 0; ks < DH / 16; ++ks) {
+        const unsigned char *row = tb + (o_row ^ (ks << 5)), *col = tb + (o_key ^ (ks << 5));
+        const bf16x8_t aq = *(const bf16x8_t*)row, bk = *(const bf16x8_t*)(col + 2 * TB);
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, bk, sc, 0, 0, 0);
+        const bf16x8_t ad = *(const bf16x8_t*)(row + TB), bv = *(const bf16x8_t*)(col + 3 * TB);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bv, dp, 0, 0, 0);
+      }
+      // lane: key column `key`; rows 8 j + 4 lk + i of this half (v = 4 j + i)
+      const int sbk = (kh * 32 + lr) >> bshift;
+      const bool diag = trow[0] < k0 + KT - 1;  // some row precedes a key of the tile: mask key > row
+      // dV^T += dO^T P and dK^T += Q^T dS, 16 rows per step in the accumulator's row permutation;
+      // each step's P and dS are formed and packed just before its MFMAs
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int v = 4 * j + i;
-          float p = __builtin_amdgcn_exp2f(fmaf(sc[v], qk_scale, ofv[i]));
-          if (diag && key > trv[i]) p = 0.f;
-          if constexpr (PLAIN) {  // unit value weights
-            pv[4 * jj + i] = p;
-            sv[4 * jj + i] = p * (dp[v] - dev[i]);
-          } else {
-            pv[4 * jj + i] = p * wv[i];
-            sv[4 * jj + i] = p * (wv[i] * dp[v] - dev[i]);
+      for (int ks = 0; ks < 2; ++ks) {
+        float pv[8], sv[8];
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+          const int j = 2 * ks + jj, r = rh * 32 + 8 * j + 4 * lk;
+          const float4 of = *(const float4*)&off_s[sbk][r];
+          const float4 de = *(const float4*)&delta_s[r];
+          const int4 tr = *(const int4*)&rows_s[par][r];
+          float4 wt = make_float4(1.f, 1.f, 1.f, 1.f);
+          if constexpr (!PLAIN)
+            if (outer) wt = *(const float4*)&wt_s[sbk][r];
+          const float ofv[4] = {of.x, of.y, of.z, of.w}, dev[4] = {de.x, de.y, de.z, de.w};
+          const float wv[4] = {wt.x, wt.y, wt.z, wt.w};
+          const int trv[4] = {tr.x, tr.y, tr.z, tr.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int v = 4 * j + i;
+            float p = __builtin_amdgcn_exp2f(fmaf(sc[v], qk_scale, ofv[i]));
+            if (diag && key > trv[i]) p = 0.f;
+            if constexpr (PLAIN) {  // unit value weights
+              pv[4 * jj + i] = p;
+              sv[4 * jj + i] = p * (dp[v] - dev[i]);
+            } else {
+              pv[4 * jj + i] = p * wv[i];
+              sv[4 * jj + i] = p * (wv[i] * dp[v] - dev[i]);
+            }
           }
         }
-      }
-      uint4 pu, su;
-      pu.x = pack_bf16x2(pv[0], pv[1]);
-      pu.y = pack_bf16x2(pv[2], pv[3]);
-      pu.z = pack_bf16x2(pv[4], pv[5]);
-      pu.w = pack_bf16x2(pv[6], pv[7]);
-      su.x = pack_bf16x2(sv[0], sv[1]);
-      su.y = pack_bf16x2(sv[2], sv[3]);
-      su.z = pack_bf16x2(sv[4], sv[5]);
-      su.w = pack_bf16x2(sv[6], sv[7]);
-      const bf16x8_t pb = *(const bf16x8_t*)&pu, sb8 = *(const bf16x8_t*)&su;
+        uint4 pu, su;
+        pu.x = pack_bf16x2(pv[0], pv[1]);
+        pu.y = pack_bf16x2(pv[2], pv[3]);
+        pu.z = pack_bf16x2(pv[4], pv[5]);
+        pu.w = pack_bf16x2(pv[6], pv[7]);
+        su.x = pack_bf16x2(sv[0], sv[1]);
+        su.y = pack_bf16x2(sv[2], sv[3]);
+        su.z = pack_bf16x2(sv[4], sv[5]);
+        su.w = pack_bf16x2(sv[6], sv[7]);
+        const bf16x8_t pb = *(const bf16x8_t*)&pu, sb8 = *(const bf16x8_t*)&su;
 #pragma unroll
-      for (int dt = 0; dt < DHH / 32; ++dt) {
-        const bf16_t* dr = Dt + (dhf * DHH + dt * 32 + lr) * QP + 16 * ks + 4 * lk;
-        const uint2 dlo = *(const uint2*)dr;
-        const uint2 dhi = *(const uint2*)(dr + 8);
-        uint4 du = make_uint4(dlo.x, dlo.y, dhi.x, dhi.y);
-        dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(bf16x8_t*)&du, pb, dv[dt], 0, 0, 0);
-        const bf16_t* qrp = Qt + (dhf * DHH + dt * 32 + lr) * QP + 16 * ks + 4 * lk;
-        const uint2 qlo = *(const uint2*)qrp;
-        const uint2 qhi = *(const uint2*)(qrp + 8);
-        uint4 qu = make_uint4(qlo.x, qlo.y, qhi.x, qhi.y);
-        dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(bf16x8_t*)&qu, sb8, dk[dt], 0, 0, 0);
+        for (int dt = 0; dt < DH / 32; ++dt) {
+          const unsigned char* lo = tb + (o_tr[0] ^ (dt << 6)) + ks * 16 * DH * 2;
+          const unsigned char* hi = tb + (o_tr[1] ^ (dt << 6)) + ks * 16 * DH * 2;
+          const uint2 dlo = lds_read_tr(lo + TB), dhi = lds_read_tr(hi + TB);
+          const uint4 du = make_uint4(dlo.x, dlo.y, dhi.x, dhi.y);
+          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8_t*)&du, pb, dv[dt], 0, 0, 0);
+          const uint2 qlo = lds_read_tr(lo), qhi = lds_read_tr(hi);
+          const uint4 qu = make_uint4(qlo.x, qlo.y, qhi.x, qhi.y);
+          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8_t*)&qu, sb8, dk[dt], 0, 0, 0);
+        }
       }
     }
     lds_barrier();
-    qc = nq;
-    hg = nh;
+    if (last_head) {
+      qc = nqcx;
+      nqcx = after;
+      par ^= 1;
+      hg = 0;
+    } else {
+      ++hg;
+    }
   }
-  if (parts > 1) {  // fp32 sums of this part; bwd_dkv_sum_kernel adds the parts
-    float* kp = P.part + (size_t)slot * (2 * 64 * DH) + (size_t)(kh * 32 + lr) * DH + dhf * DHH;
-    float* vp = kp + 64 * DH;
+
+  // add the row halves: wave (kh, 0) takes dK, wave (kh, 1) takes dV
+  {
+    float* x = (float*)tiles + (size_t)wave * (32 * DH / 2) * 2;  // 32 keys x DH sums of this wave's other matrix
 #pragma unroll
-    for (int dt = 0; dt < DHH / 32; ++dt)
+    for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        const int d0 = dt * 32 + 8 * v4 + 4 * lk;
-        *(float4*)(kp + d0) = make_float4(dk[dt][4 * v4], dk[dt][4 * v4 + 1], dk[dt][4 * v4 + 2], dk[dt][4 * v4 + 3]);
-        *(float4*)(vp + d0) = make_float4(dv[dt][4 * v4], dv[dt][4 * v4 + 1], dv[dt][4 * v4 + 2], dv[dt][4 * v4 + 3]);
+        const floatx16_t& o = rh ? dk[dt] : dv[dt];
+        *(float4*)(x + ((dt * 4 + v4) * 64 + lane) * 4) = make_float4(o[4 * v4], o[4 * v4 + 1], o[4 * v4 + 2], o[4 * v4 + 3]);
       }
-    return;
+    lds_barrier();
+    x = (float*)tiles + (size_t)(wave ^ 1) * (32 * DH / 2) * 2;
+    const float sm = rh ? 1.f : P.sm_scale;
+    float* fp = P.part + (size_t)slot * (2 * 64 * DH) + (size_t)(rh * 64 + kh * 32 + lr) * DH;
+    bf16_t* op = (bf16_t*)(rh ? P.dV : P.dK) + (((size_t)bi * n + min(key, n - 1)) * P.Hkv + g) * DH;
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const floatx16_t& o = rh ? dv[dt] : dk[dt];
+        const float4 y = *(const float4*)(x + ((dt * 4 + v4) * 64 + lane) * 4);
+        // rows ascend from half 0 to half 1 in both waves' sums
+        const float4 r = rh ? make_float4(y.x + o[4 * v4], y.y + o[4 * v4 + 1], y.z + o[4 * v4 + 2], y.w + o[4 * v4 + 3])
+                            : make_float4(o[4 * v4] + y.x, o[4 * v4 + 1] + y.y, o[4 * v4 + 2] + y.z, o[4 * v4 + 3] + y.w);
+        const int d0 = dt * 32 + 8 * v4 + 4 * lk;
+        if (parts > 1) *(float4*)(fp + d0) = r;  // bwd_dkv_sum_kernel adds the parts
+        else if (key < n)
+          *(uint2*)(op + d0) = make_uint2(pack_bf16x2(r.x * sm, r.y * sm), pack_bf16x2(r.z * sm, r.w * sm));
+      }
   }
-  if (!kvalid) return;
-  const size_t off = (((size_t)bi * n + key) * P.Hkv + g) * DH + dhf * DHH;
-  bf16_t* dkp = (bf16_t*)P.dK + off;
-  bf16_t* dvp = (bf16_t*)P.dV + off;
-  const float sm = P.sm_scale;
-#pragma unroll
-  for (int dt = 0; dt < DHH / 32; ++dt)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      const int d0 = dt * 32 + 8 * v4 + 4 * lk;
-      uint32_t w0 = pack_bf16x2(dk[dt][4 * v4 + 0] * sm, dk[dt][4 * v4 + 1] * sm);
-      uint32_t w1 = pack_bf16x2(dk[dt][4 * v4 + 2] * sm, dk[dt][4 * v4 + 3] * sm);
-      *(uint2*)(dkp + d0) = make_uint2(w0, w1);
-      w0 = pack_bf16x2(dv[dt][4 * v4 + 0], dv[dt][4 * v4 + 1]);
-      w1 = pack_bf16x2(dv[dt][4 * v4 + 2], dv[dt][4 * v4 + 3]);
-      *(uint2*)(dvp + d0) = make_uint2(w0, w1);
-    }
 }
 
 template <int DH, bool PLAIN>

@@ -209,7 +209,7 @@ struct BwdArgs {
   int* tile_off;
   int* tile_rows;
   // the dK/dV pass's jobs (bf16 path, selections): a tile's row list in one or
-  // several parts of about split_chunks chunks of 32 rows; parts of a divided
+  // several parts of about split_chunks chunks of 64 rows; parts of a divided
   // tile leave fp32 sums in `part` and are added afterwards
   int4* jobs;             // [b Hkv ceil(n/64) + split_slots] (tile, part, parts, slot of the part)
   int* job_count;         // [1]
@@ -224,16 +224,16 @@ struct BwdArgs {
   const int32_t* doc;     // [b, NB] first block of each block's document, or null
   uint32_t* queue;        // [2] job counters of the bf16 pass kernels' work queues (reset by the launch)
 };
-// longest sequence of the bf16 attention backward (query chunks of 32 tracked in LDS)
+// longest sequence of the bf16 attention backward (query chunks tracked in LDS)
 constexpr int BWD_MAX_SEQ = 262144;
 // How the dK/dV pass divides its row lists.  A key tile is attended by its own
 // rows and by every row that selected one of its blocks, so early tiles have
 // lists several times the average and, with few (batch, group) pairs, one of
 // them alone takes longer than the rest.  Parts of about 1/2048 of all chunks
-// (four for each of the 512 resident workgroups) and at least 8 chunks keep the
+// (four for each of the 512 resident workgroups) and at least 4 chunks keep the
 // last wave short; a divided tile has at most twice chunks / split_chunks
 // parts, which bounds the slots.  28/4 heads, 5003 tokens, K = 32 (316 tiles):
-// the pass 1311 -> 512 us and 32 us for adding the parts.
+// the pass 1311 -> 512 us (318 since its rows are staged once) and 31 us for adding the parts.
 struct BwdSplit {
   int chunks;
   long long slots;
@@ -241,9 +241,9 @@ struct BwdSplit {
 inline BwdSplit bwd_split(int b, int Hkv, int n, int B, int K) {
   const long long Z = (long long)b * Hkv, tiles = Z * ((n + 63) / 64);
   const long long rows = Z * n * (K + 1) * (B > 64 ? 2 : 1);  // list entries, at most
-  const long long all = rows / 32 + tiles;
+  const long long all = rows / 64 + tiles;
   BwdSplit r;
-  r.chunks = (int)std::max<long long>(8, (all + 2047) / 2048);
+  r.chunks = (int)std::max<long long>(4, (all + 2047) / 2048);
   r.slots = 2 * all / r.chunks + 1;
   return r;
 }
