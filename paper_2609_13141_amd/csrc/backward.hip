@@ -276,40 +276,68 @@ __global__ void fill_f32_kernel(float* p, size_t n, float v) {
 // ---- bf16 path ------------------------------------------------------------------
 constexpr float BLOG2E = 1.4426950408889634f;
 
+// LDS tiles of the two passes: rows of DH values without padding, the 16-byte
+// chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
+// (the row-major operand reads) then lie in distinct banks, and so do the four
+// rows x 32 dimensions that half a wave takes with a transposing read.
+template <int DH>
+__device__ __forceinline__ int lds_swz(int r) {
+  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+template <int DH>
+__device__ __forceinline__ int lds_chunk(int r, int c) { return r * DH + ((c ^ lds_swz<DH>(r)) << 3); }
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+// ds_read_b64_tr_b16: in each group of 16 lanes, lane 4 j + a names 4 consecutive
+// values of row j of a 4 x 16 tile, and lane i receives column i (rows 0..3).
+__device__ __forceinline__ uint2 lds_read_tr(const unsigned char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p));
+}
+
 // Pass 1 (dQ and the per-head block sums of ds): one workgroup = 4 waves =
-// 128 queries of one (batch, head), each lane owning one query of S^T = K Q^T
-// (v_mfma_f32_32x32x16_bf16), with dP^T = V dO^T computed the same way;
-// dS^T = P^T (dP^T - Delta) is formed in registers and fed back as the B
-// operand of dQ^T += K^T dS^T (K staged transposed in LDS, read in the
-// accumulator's key permutation).  The key tiles any query of the workgroup
-// attends are flagged in LDS first; each tile's K and V are loaded into
-// registers while the previous tile is multiplied.  Sub-blocks of
-// 2^LSB = min(B, 64) keys carry one bias per query; a sub-block of an
-// accumulator element is known at compile time (the lane-dependent part of
-// its key index is below 8).  Each lane walks its query's ascending
-// selection row from global memory (the next slot read one slot ahead) and
-// writes a slot's block sum once the slot's last sub-block is done; a tile is
-// processed as two halves of 32 keys to keep the live registers low enough
-// for two workgroups per compute unit.
-template <int DH, int LSB, bool PLAIN>
-__device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtile, const int h, const int bi) {
-  constexpr int KP = DH + 8;
-  constexpr int TP = 64 + 4;
-  constexpr int KPG = DH / 32;   // keys per thread in the tile staging
+// 128 query rows of one batch entry and KV group, 128 / G consecutive positions x
+// the group's G heads as in the forward (the key tiles the rows attend are the
+// union over the positions only); a wave none of whose rows attends a key of
+// the tile skips its products (SKIP, grouped queries).  Each lane owns one query
+// of S^T = K Q^T (v_mfma_f32_32x32x16_bf16), with dP^T = V dO^T computed the
+// same way; dS^T = P^T (dP^T - Delta) is formed in registers and fed back as the
+// B operand of dQ^T += K^T dS^T, whose A operand is read from the same K rows
+// with the transposing LDS read, in the accumulator's key permutation.  The key
+// tiles any query of the workgroup attends are flagged in LDS first; a tile's
+// K and V are loaded into registers while the previous tile is multiplied and
+// written to the other of two buffers after it: one barrier per tile.
+// Sub-blocks of 2^LSB = min(B, 64) keys carry one bias per query; a sub-block of
+// an accumulator element is known at compile time (the lane-dependent part of
+// its key index is below 8).  Each lane walks its query's ascending selection
+// row from global memory (the next slot read one slot ahead) and writes a
+// slot's block sum once the slot's last sub-block is done; a tile is processed
+// as two halves of 32 keys to keep the live registers low enough for two
+// workgroups per compute unit.  28/4 heads, 16384 tokens, K = 32: 3.57 ms, 4.20 with
+// one head per workgroup, a transposed K copy and two barriers; 4 x 4096, 32/32
+// heads: 1.33 ms, 1.39 before.
+// heads of a KV group that share a workgroup's rows (1 when a group has more heads than rows)
+__host__ __device__ inline int bwd_dq_heads(int G) { return G <= 128 ? G : 1; }
+
+template <int DH, int LSB, bool PLAIN, bool SKIP>
+__device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtile, const int unit, const int bi) {
   constexpr int C8 = DH / 8;
+  constexpr int KPT = 64 * C8 / 256;  // keys per thread in the tile staging ...
+  constexpr int KS = 256 / C8;        // ... this many apart
   constexpr int NSUB = 64 >> LSB;
-  __shared__ __align__(16) bf16_t Ks[64 * KP];
-  __shared__ __align__(16) bf16_t Vs[64 * KP];
-  __shared__ __align__(16) bf16_t Kt[DH * TP];
+  constexpr int TB = 64 * DH * 2;     // bytes of a tile
+  __shared__ __align__(16) unsigned char tiles[2 * 2 * TB];  // two buffers of K and V
   __shared__ uint32_t need[BWD_MAX_SEQ / 64 / 32];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 31, lk = lane >> 5;
-  const int G = P.H / P.Hkv, g = h / G;
+  const int G = P.H / P.Hkv, PG = bwd_dq_heads(G), QPT = 128 / PG;
   const int n = P.n, B = P.B;
   const int qrow = wave * 32 + lr;  // query row of this lane in the workgroup
-  const int t = qtile * 128 + qrow;
-  const bool qvalid = t < n;
+  const int pl = qrow / PG, h = unit * PG + (qrow - pl * PG), g = unit * PG / G;
+  const int t0 = qtile * QPT;       // first position of the workgroup
+  const int t = t0 + pl;
+  const bool qvalid = pl < QPT && t < n;
   const int beta = qvalid ? t / B : -1;
   const bool gated = P.mode == SAS_MODE_GATED;
   const bool dense = P.mode == SAS_MODE_DENSE;
@@ -321,10 +349,10 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
   const int ntiles = (n + 63) / 64;
   const int NB = (n + B - 1) / B;
   const size_t grow = ((size_t)bi * P.Hkv + g) * n;
-  const int t_hi = min(n, qtile * 128 + 128) - 1;
+  const int t_hi = min(n, t0 + QPT) - 1;
   const int last_tile = t_hi / 64;
   const int fb = qvalid ? doc_first(P.doc, bi, NB, t, B) : 0;  // first block of the query's document
-  const int first_tile = doc_first(P.doc, bi, NB, qtile * 128, B) * B / 64;
+  const int first_tile = doc_first(P.doc, bi, NB, t0, B) * B / 64;
 
   bf16x8_t qb[DH / 16], dob[DH / 16];
   {
@@ -376,16 +404,17 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
   const bf16_t* Vg = (const bf16_t*)P.V + (size_t)g * DH;
   const size_t kstride = (size_t)P.Hkv * DH;
   const size_t kbase = (size_t)bi * n;
-  const int c8 = tid % C8, kg = tid / C8;
-  uint4 rk[KPG], rv[KPG];
+  const int c8 = tid % C8, kg = tid / C8;  // staging role: keys kg + KS q, 16-byte piece c8
+  uint4 rk[KPT], rv[KPT];
   float r_lg[NSUB];  // full scope: this query's log gates of the tile's blocks
   auto prefetch = [&](int kt) {
+    // unconditional loads (a branch around a load waits for those in flight):
+    // keys past the end repeat the last one and are zeroed on their way to LDS
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) {
-      const int key = kt * 64 + kg * KPG + q;
-      const size_t go = (kbase + key) * kstride + c8 * 8;
-      rk[q] = key < n ? *(const uint4*)(Kg + go) : make_uint4(0, 0, 0, 0);
-      rv[q] = key < n ? *(const uint4*)(Vg + go) : make_uint4(0, 0, 0, 0);
+    for (int q = 0; q < KPT; ++q) {
+      const size_t go = (kbase + min(kt * 64 + kg + KS * q, n - 1)) * kstride + c8 * 8;
+      rk[q] = *(const uint4*)(Kg + go);
+      rv[q] = *(const uint4*)(Vg + go);
     }
     if (full) {
 #pragma unroll
@@ -395,26 +424,28 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
       }
     }
   };
-  auto commit = [&]() {
+  auto commit = [&](int kt, int buf) {
+    bf16_t* kb = (bf16_t*)(tiles + buf * 2 * TB);
+    if (kt * 64 + 64 > n) {
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) {
-      *(uint4*)(Ks + (kg * KPG + q) * KP + c8 * 8) = rk[q];
-      *(uint4*)(Vs + (kg * KPG + q) * KP + c8 * 8) = rv[q];
+      for (int q = 0; q < KPT; ++q)
+        if (kt * 64 + kg + KS * q >= n) rk[q] = rv[q] = make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int sh = (e & 1) * 16, wd = e >> 1;
-      bf16_t* dst = Kt + (c8 * 8 + e) * TP + kg * KPG;
-      uint32_t x[KPG];
-#pragma unroll
-      for (int q = 0; q < KPG; ++q) x[q] = (((const uint32_t*)&rk[q])[wd] >> sh) & 0xffffu;
-      if constexpr (KPG == 4) {
-        *(uint2*)dst = make_uint2(x[0] | (x[1] << 16), x[2] | (x[3] << 16));
-      } else {
-        *(uint32_t*)dst = x[0] | (x[1] << 16);
-      }
+    for (int q = 0; q < KPT; ++q) {
+      *(uint4*)(kb + lds_chunk<DH>(kg + KS * q, c8)) = rk[q];
+      *(uint4*)(kb + 64 * DH + lds_chunk<DH>(kg + KS * q, c8)) = rv[q];
     }
   };
+  // byte offsets of this lane's operands in a tile (see the dK/dV pass): rows lr,
+  // chunk 2 ks + lk; columns of row 4 lk + 8 half + (lane % 16) / 4
+  uint32_t o_row = lr * DH * 2 + ((lk ^ lds_swz<DH>(lr)) << 4);
+  uint32_t o_tr[2];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    const int r = 4 * lk + 8 * hf + ((lane & 15) >> 2);
+    o_tr[hf] = r * DH * 2 + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ lds_swz<DH>(r)) << 4) + (lane & 1) * 8;
+  }
 
   // the walk over this query's slots: slot `cur` (block next_sel, bias b_cur) and the
   // one after it (read one slot ahead, so the read is done by the time it is needed)
@@ -428,12 +459,16 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
   if (next_sel < 0) next_sel = 0x7fffffff;
   float blk_acc = 0.f;   // full scope: running sum of a block wider than a tile
   float slot_acc = 0.f;  // the current slot's running sum (a block may span two tiles)
-  int kt = next_set(need, 0, ntiles);
-  if (kt < ntiles) prefetch(kt);
+  int kt = next_set(need, 0, ntiles), buf = 0;
+  if (kt < ntiles) {
+    prefetch(kt);
+    commit(kt, 0);
+  }
   while (kt < ntiles) {
-    commit();
-    lds_barrier();
+    lds_barrier();  // the tile is staged; every wave is done with the other buffer
     const int k0 = kt * 64;
+    const unsigned char* const tb = tiles + buf * 2 * TB;
+    asm volatile("" : "+v"(o_row), "+v"(o_tr[0]), "+v"(o_tr[1]));  // (formed anew per tile: kept, they would spill)
 
     // per sub-block: offset (log2-domain bias - LSE; -inf: neither attended nor
     // receiving a gradient), value weight, attended, selection slot
@@ -484,7 +519,13 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
     const int nkt = next_set(need, kt + 1, ntiles);
     if (nkt < ntiles) prefetch(nkt);
 
-    const bool diag = k0 + 63 > qtile * 128;  // keys past some query of the workgroup: mask key > t
+    bool any = !SKIP;
+    if constexpr (SKIP) {
+#pragma unroll
+      for (int sb = 0; sb < NSUB; ++sb) any = any || offs[sb] != -INFINITY;
+    }
+    if (!SKIP || __builtin_amdgcn_ballot_w64(any) != 0) {
+    const bool diag = k0 + 63 > t0;  // keys past some query of the workgroup: mask key > t
     float dsum[NSUB];
 #pragma unroll
     for (int sb = 0; sb < NSUB; ++sb) dsum[sb] = 0.f;
@@ -500,9 +541,10 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
       }
 #pragma unroll
       for (int ks = 0; ks < DH / 16; ++ks) {
-        const bf16x8_t a = *(const bf16x8_t*)(Ks + (st * 32 + lr) * KP + ks * 16 + lk * 8);
+        const unsigned char* row = tb + (o_row ^ (ks << 5)) + st * 32 * DH * 2;
+        const bf16x8_t a = *(const bf16x8_t*)row;
         sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb[ks], sc, 0, 0, 0);
-        const bf16x8_t av = *(const bf16x8_t*)(Vs + (st * 32 + lr) * KP + ks * 16 + lk * 8);
+        const bf16x8_t av = *(const bf16x8_t*)(row + TB);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, dob[ks], dp, 0, 0, 0);
       }
       // P, dS^T and the block sums.  PLAIN (no value weights, no straight-through gradient): a
@@ -535,9 +577,8 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
         const bf16x8_t pb = *(const bf16x8_t*)&su;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt) {
-          const bf16_t* kr = Kt + (dt * 32 + lr) * TP + 16 * ks + 4 * lk;
-          const uint2 lo = *(const uint2*)kr;
-          const uint2 hi = *(const uint2*)(kr + 8);
+          const uint2 lo = lds_read_tr(tb + (o_tr[0] ^ (dt << 6)) + ks * 16 * DH * 2);
+          const uint2 hi = lds_read_tr(tb + (o_tr[1] ^ (dt << 6)) + ks * 16 * DH * 2);
           uint4 u = make_uint4(lo.x, lo.y, hi.x, hi.y);
           dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(bf16x8_t*)&u, pb, dq[dt], 0, 0, 0);
         }
@@ -562,7 +603,9 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
         }
       }
     }
-    lds_barrier();
+    }
+    buf ^= 1;
+    if (nkt < ntiles) commit(nkt, buf);
     kt = nkt;
   }
 
@@ -587,15 +630,17 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
 // One job per workgroup (grid = job count, no queue) or the work queue.
 // two workgroups per compute unit where the registers allow it without spills
 // (one sub-block per tile, or dh = 64)
-template <int DH, int LSB, bool PLAIN>
+template <int DH, int LSB, bool PLAIN, bool SKIP>
 __global__ void __launch_bounds__(256, LSB == 6 || DH == 64 ? 2 : 1) bwd_dq_bf16_kernel(BwdArgs P) {
-  const int nqt = (P.n + 127) / 128, per = P.H * P.b;
+  const int PG = bwd_dq_heads(P.H / P.Hkv), qpt = 128 / PG;
+  const int nqt = (P.n + qpt - 1) / qpt, units = P.H / PG, per = units * P.b;
   const int njobs = nqt * per;
   for (int it = 0;; ++it) {
     const int job = P.queue ? queue_next_job(P.queue) : (it == 0 ? (int)blockIdx.x : njobs);
     if (job >= njobs) break;
-    const int r = job % per;  // the longest (last) query tiles first, heads and batch inside
-    bwd_dq_bf16_job<DH, LSB, PLAIN>(P, nqt - 1 - job / per, r % P.H, r / P.H);
+    const int r = job % per;  // the longest (last) query tiles first, groups and batch inside
+    __syncthreads();          // the previous job is done with LDS
+    bwd_dq_bf16_job<DH, LSB, PLAIN, SKIP>(P, nqt - 1 - job / per, r % units, r / units);
   }
 }
 
@@ -741,25 +786,6 @@ __global__ void __launch_bounds__(256) bwd_dkv_sum_kernel(const int2* __restrict
   }
 }
 
-// LDS tiles of the dK/dV pass: rows of DH values without padding, the 16-byte
-// chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
-// (the row-major operand reads) then lie in distinct banks, and so do the four
-// rows x 32 dimensions that half a wave takes with a transposing read.
-template <int DH>
-__device__ __forceinline__ int lds_swz(int r) {
-  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
-template <int DH>
-__device__ __forceinline__ int lds_chunk(int r, int c) { return r * DH + ((c ^ lds_swz<DH>(r)) << 3); }
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-// ds_read_b64_tr_b16: in each group of 16 lanes, lane 4 j + a names 4 consecutive
-// values of row j of a 4 x 16 tile, and lane i receives column i (rows 0..3).
-__device__ __forceinline__ uint2 lds_read_tr(const unsigned char* p) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p));
-}
-
 // Pass 2 (dK, dV): one workgroup of 4 waves per 64 keys of one (batch, KV
 // group).  The rows are those of the tile's list (selections), or, when every
 // earlier block is attended (DENSE, full scope), the consecutive rows from the
@@ -827,14 +853,22 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
   // the previous job of this workgroup is done with LDS
   __syncthreads();
   const int c8 = tid % C8, sr = tid / C8;  // staging role: rows sr + RS i, 16-byte piece c8
+  {
+    uint4 kv[NR], vv[NR];
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int kr = sr + RS * i;
-    const size_t off = (((size_t)bi * n + min(k0 + kr, n - 1)) * P.Hkv + g) * DH + c8 * 8;
-    uint4 kv = *(const uint4*)((const bf16_t*)P.Kt + off), vv = *(const uint4*)((const bf16_t*)P.V + off);
-    if (k0 + kr >= n) kv = vv = make_uint4(0, 0, 0, 0);
-    *(uint4*)(Ks + lds_chunk<DH>(kr, c8)) = kv;
-    *(uint4*)(Vs + lds_chunk<DH>(kr, c8)) = vv;
+    for (int i = 0; i < NR; ++i) {
+      const size_t off = (((size_t)bi * n + min(k0 + sr + RS * i, n - 1)) * P.Hkv + g) * DH + c8 * 8;
+      kv[i] = *(const uint4*)((const bf16_t*)P.Kt + off);
+      vv[i] = *(const uint4*)((const bf16_t*)P.V + off);
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const uint32_t keep = k0 + sr + RS * i < n ? 0xffffffffu : 0u;  // keys past the end: zero
+      kv[i] = make_uint4(kv[i].x & keep, kv[i].y & keep, kv[i].z & keep, kv[i].w & keep);
+      vv[i] = make_uint4(vv[i].x & keep, vv[i].y & keep, vv[i].z & keep, vv[i].w & keep);
+      *(uint4*)(Ks + lds_chunk<DH>(sr + RS * i, c8)) = kv[i];
+      *(uint4*)(Vs + lds_chunk<DH>(sr + RS * i, c8)) = vv[i];
+    }
   }
   // without a list: the chunks that reach the tile (their rows lie in its blocks, or,
   // every earlier block being attended, their earliest row's document starts in time)
@@ -870,56 +904,58 @@ __device__ __forceinline__ void bwd_dkv_bf16_job(const BwdArgs& P, const int kti
   uint4 rq[NR], rd[NR];
   float r_lse = 0.f, r_delta = 0.f, r_lg = 0.f;
   uint32_t r_mw = 0;
-  int r_fb = 0;  // first block of the row's document
+  int r_doc = 0;  // the row's entry of the packing table
+  // the next item's values: unconditional loads from clamped addresses, left as
+  // they arrive until commit (a branch or an operation on one waits for all in flight)
   auto prefetch = [&](int par, int hg) {
     const int h = g * G + hg;
+    int t[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) t[i] = min(rows_s[par][sr + RS * i], n - 1);
+    const int tb = min(rows_s[par][bq], n - 1);
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      const int t = rows_s[par][sr + RS * i];
-      const size_t off = (((size_t)bi * n + min(t, n - 1)) * H + h) * DH + c8 * 8;
+      const size_t off = (((size_t)bi * n + t[i]) * H + h) * DH + c8 * 8;
       rq[i] = *(const uint4*)((const bf16_t*)P.Q + off);
       rd[i] = *(const uint4*)((const bf16_t*)P.dO + off);
-      if (t >= n) rq[i] = rd[i] = make_uint4(0, 0, 0, 0);
     }
-    const int t = rows_s[par][bq];
-    const size_t hr = ((size_t)bi * H + h) * n + min(t, n - 1);
-    if (wave == 0) r_delta = t < n ? P.delta[hr] : 0.f;
+    const size_t hr = ((size_t)bi * H + h) * n + tb;
+    if (wave == 0) r_delta = P.delta[hr];
     if (bsb < nsb) {
-      const int kstart = k0 + (bsb << bshift), m = kstart / B;
-      r_lse = t < n ? P.lse[hr] : 0.f;
-      r_fb = t < n ? doc_first(P.doc, bi, NB, t, B) : 0;
-      r_mw = 0u;
-      r_lg = 0.f;
-      if (t < n && kstart <= t && m != t / B) {
-        r_mw = use_list ? P.selmask[(grow + t) * NW + (m >> 5)] : 0u;
-        r_lg = gated && (use_list || fullatt) ? P.log_gate[(grow + t) * NB + m] : 0.f;
-      }
+      const int m = min((k0 + (bsb << bshift)) / B, NB - 1);
+      r_lse = P.lse[hr];
+      if (P.doc) r_doc = P.doc[(size_t)bi * NB + tb / B];
+      if (use_list) r_mw = P.selmask[(grow + tb) * NW + (m >> 5)];
+      if (gated && (use_list || fullatt)) r_lg = P.log_gate[(grow + tb) * NB + m];
     }
   };
   auto commit = [&](int par) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      *(uint4*)(Qs + lds_chunk<DH>(sr + RS * i, c8)) = rq[i];
-      *(uint4*)(Ds + lds_chunk<DH>(sr + RS * i, c8)) = rd[i];
+      const uint32_t keep = rows_s[par][sr + RS * i] < n ? 0xffffffffu : 0u;  // no row: zero
+      const int o = lds_chunk<DH>(sr + RS * i, c8);
+      *(uint4*)(Qs + o) = make_uint4(rq[i].x & keep, rq[i].y & keep, rq[i].z & keep, rq[i].w & keep);
+      *(uint4*)(Ds + o) = make_uint4(rd[i].x & keep, rd[i].y & keep, rd[i].z & keep, rd[i].w & keep);
     }
-    if (wave == 0) delta_s[bq] = r_delta;
+    const int t = rows_s[par][bq];
+    if (wave == 0) delta_s[bq] = t < n ? r_delta : 0.f;
     if (bsb < nsb) {
-      const int t = rows_s[par][bq], kstart = k0 + (bsb << bshift), m = kstart / B;
+      const int kstart = k0 + (bsb << bshift), m = kstart / B;
+      const int fb = min(max(r_doc, 0), t / B);  // first block of the row's document (doc_first)
       float bb = -INFINITY, w = 1.f;
       if (t < n && kstart <= t) {
-        if (m == t / B || (dense && m >= r_fb)) {
+        if (m == t / B || (dense && m >= fb)) {
           bb = 0.f;
-        } else if ((fullatt && m >= r_fb) || ((r_mw >> (m & 31)) & 1u)) {
+        } else if ((fullatt && m >= fb) || (use_list && ((r_mw >> (m & 31)) & 1u))) {
           const bool gate = gated && !ste;
           bb = gate && !outer ? r_lg * BLOG2E : 0.f;
           if (gate && outer) w = __builtin_amdgcn_exp2f(r_lg * BLOG2E);
         }
       }
-      off_s[bsb][bq] = bb - r_lse * BLOG2E;
+      off_s[bsb][bq] = bb - (t < n ? r_lse : 0.f) * BLOG2E;
       if constexpr (!PLAIN) wt_s[bsb][bq] = w;
     }
   };
-
   // byte offsets of this lane's operands in a tile; a step or dimension block is an
   // exclusive-or of the chunk bits.  Rows: row rh 32 + lr of Q / dO and kh 32 + lr of
   // K / V, chunk 2 ks + lk.  Columns (transposing read): dimensions 32 dt + 16 (lane
@@ -1132,22 +1168,20 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
   const int lsb = P.B >= 64 ? 6 : (P.B == 32 ? 5 : 4);
   // no value weights and no straight-through gradient: the plain elementwise step
   const bool plain = !(P.mode == SAS_MODE_GATED && (P.outer || P.ste));
+  const int pg = bwd_dq_heads(P.H / P.Hkv);
   void (*dq)(BwdArgs);
-  if (plain)
-    dq = P.dh == 128 ? (lsb == 6 ? bwd_dq_bf16_kernel<128, 6, true> : lsb == 5 ? bwd_dq_bf16_kernel<128, 5, true>
-                                                                             : bwd_dq_bf16_kernel<128, 4, true>)
-                     : (lsb == 6 ? bwd_dq_bf16_kernel<64, 6, true> : lsb == 5 ? bwd_dq_bf16_kernel<64, 5, true>
-                                                                            : bwd_dq_bf16_kernel<64, 4, true>);
-  else
-    dq = P.dh == 128 ? (lsb == 6 ? bwd_dq_bf16_kernel<128, 6, false> : lsb == 5 ? bwd_dq_bf16_kernel<128, 5, false>
-                                                                              : bwd_dq_bf16_kernel<128, 4, false>)
-                     : (lsb == 6 ? bwd_dq_bf16_kernel<64, 6, false> : lsb == 5 ? bwd_dq_bf16_kernel<64, 5, false>
-                                                                             : bwd_dq_bf16_kernel<64, 4, false>);
+#define DQ_PICK2(DH, LSB, PLAIN) \
+  (pg > 1 ? bwd_dq_bf16_kernel<DH, LSB, PLAIN, true> : bwd_dq_bf16_kernel<DH, LSB, PLAIN, false>)
+#define DQ_PICK(DH, LSB) (plain ? DQ_PICK2(DH, LSB, true) : DQ_PICK2(DH, LSB, false))
+  if (P.dh == 128) dq = lsb == 6 ? DQ_PICK(128, 6) : lsb == 5 ? DQ_PICK(128, 5) : DQ_PICK(128, 4);
+  else dq = lsb == 6 ? DQ_PICK(64, 6) : lsb == 5 ? DQ_PICK(64, 5) : DQ_PICK(64, 4);
+#undef DQ_PICK
+#undef DQ_PICK2
   auto dkv = P.dh == 128 ? (plain ? bwd_dkv_bf16_kernel<128, true> : bwd_dkv_bf16_kernel<128, false>)
                          : (plain ? bwd_dkv_bf16_kernel<64, true> : bwd_dkv_bf16_kernel<64, false>);
   const bool lists = Q.tile_rows != nullptr;
   // list jobs are counted on the GPU: at most one per tile and one per slot
-  const long long jq = (long long)cdiv(P.n, 128) * P.H * P.b;
+  const long long jq = (long long)cdiv(P.n, 128 / pg) * (P.H / pg) * P.b;
   const long long jk = (long long)ntk * P.Hkv * P.b + (lists ? P.split_slots : 0);
   const int rq = resident_workgroups(dq, 256), rk = resident_workgroups(dkv, 256);
   if (rq <= 0 || rk <= 0 || jq > INT32_MAX || jk > INT32_MAX) return hipErrorInvalidValue;
