@@ -12,15 +12,17 @@
 // partner lane l^32.  The exponentiated scores P^T stay in registers and are
 // fed straight back as the B operand of O^T = V^T P^T: the key order in which
 // the accumulator holds P^T is a fixed permutation of the key index, and V^T
-// is read from LDS in that same permutation, so no shuffle is needed.
+// is read in that same permutation from the tile's V rows with the transposing
+// LDS read, so neither a shuffle nor a transposed copy is needed.
 //
 // The 64-key tiles that any query of the workgroup attends are flagged in an
 // LDS bitmask first (every query's current block and selected blocks, or
 // every earlier tile for DENSE and the full scope); each flagged tile's K and
-// V are loaded into registers while the previous tile is multiplied, then
-// written to LDS (K row-major, V transposed).  The selection rows of the
-// workgroup's queries are staged in LDS, and each lane walks its ascending
-// list with a cursor while the tiles advance.
+// V rows go straight to LDS (global_load_lds) while the previous tile is
+// multiplied from the other of two buffers: one barrier per tile, no staging
+// registers (28/4 heads, 16384 tokens, K = 32: 2.19 -> 2.11 ms against staging
+// through registers with a transposed V copy; dense, 8 x 2048: 0.44 -> 0.41).  Each lane walks its ascending selection row in global memory,
+// the next slot read one slot ahead, while the tiles advance.
 //
 // Per (query t, key i) with m = block(i) = i / B and beta = block(t):
 //   m == beta : current block, causal (i <= t), unit gate;
@@ -47,33 +49,21 @@ __global__ void fill_u32_kernel(uint32_t* p, int n, uint32_t v) {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
+typedef __attribute__((address_space(3))) void attn_lds_t;
+
 template <int DH, int LSB, bool OUTER, bool SKIP>
 __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile, const int g, const int bi,
                                               const int tlo, const int thi, const int slot) {
-  constexpr int KP = DH + 8;    // K tile row pitch (elements)
-  // V^T tile: head dimension d starts at (d / 8) * VGS + (d % 8) * VP
-  // elements (rows 96 apart, groups of 8 rows 776 apart).  A row holds the
-  // tile's 64 keys in 8 pairs of 4-key chunks: pair 2 j + h holds keys
-  // 16 j + 4 h + 0..3 and 16 j + 8 + 4 h + 0..3, the 8 keys one lane group
-  // (h) feeds to the PV product's MFMA step j, so an operand is one 16-byte
-  // read.  The strides were chosen by measuring the LDS bank-conflict
-  // counter for these exact access patterns: the operand reads run without
-  // conflicts and the staging writes (rows 8 apart) with two-way ones.
-  constexpr int VP = 96;
-  constexpr int VGS = 8 * VP + 8;
-  constexpr int KPG = DH / 32;  // keys per thread in the tile staging
   constexpr int C8 = DH / 8;
   constexpr int NSUB = 64 >> LSB;  // sub-blocks of min(B, 64) keys in a tile
-  constexpr int KMAX = 32;
-  __shared__ __align__(16) bf16_t Ks[64 * KP];
-  __shared__ __align__(16) bf16_t Vt[DH / 8 * VGS];
-  // selection slots of the workgroup's queries, slot-major ([KMAX][128]):
-  // the lanes of a wave read consecutive words
-  __shared__ int sel_s[128 * KMAX];
-  __shared__ float sbias_s[128 * KMAX];
+  constexpr int TB = 64 * DH * 2;  // bytes of a tile
+  constexpr int NL = 64 * C8 / 256;  // 16-byte pieces of K (and of V) per thread and tile
+  // two buffers of K and V (4 TB bytes; dynamic, because the compiler makes every read
+  // of a static array wait for the direct-to-LDS loads in flight)
+  extern __shared__ __align__(16) unsigned char tiles[];
   __shared__ uint32_t need[ATTN_MAX_SEQ / 64 / 32];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lk = lane >> 5;
   // the workgroup's 128 rows: QPT consecutive positions x the G heads of kv
   // group g (the heads of a group share the selection at a position, so the
@@ -111,7 +101,7 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
     }
   }
 
-  // selection rows (the lane pair lk = 0, 1 splits the slots) and the tile flags
+  // the tile flags
   for (int w = tid; w < (ntiles + 31) / 32; w += 256) {
     const int lo = w * 32;
     uint32_t bits = 0;
@@ -120,22 +110,29 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
     if (lo + 31 < first_tile) bits = 0;
     need[w] = bits;
   }
-  if (Kn > 0 && qvalid) {
-    const size_t row = (grow + t) * Kn;
-    for (int k = lk; k < Kn; k += 2) {
-      sel_s[k * 128 + qrow] = P.sel[row + k];
-      if (gated) sbias_s[k * 128 + qrow] = P.sel_bias[row + k];
-    }
-  }
+  // this query's selection row: slots are ascending historical blocks, -1 padded
+  const size_t srow = (grow + (qvalid ? t : 0)) * (size_t)Kn;
+  auto sel_at = [&](int k) -> int { return P.sel[srow + min(k, Kn - 1)]; };  // Kn > 0
+  int skip_slots = 0;  // slots consumed before tile tlo
   __syncthreads();
-  if (!every && qvalid && lk == 0) {
-    for (int tl = (beta * B) / 64; tl <= t / 64; ++tl) atomicOr(&need[tl >> 5], 1u << (tl & 31));
-    for (int k = 0; k < Kn; ++k) {
-      const int m = sel_s[k * 128 + qrow];
-      if (m < 0 || m >= beta) break;  // slots are ascending historical blocks, -1 padded
-      for (int tl = (m * B) / 64; tl <= ((m + 1) * B - 1) / 64; ++tl) atomicOr(&need[tl >> 5], 1u << (tl & 31));
+  if (!every && qvalid) {
+    if (lk == 0)
+      for (int tl = (beta * B) / 64; tl <= t / 64; ++tl) atomicOr(&need[tl >> 5], 1u << (tl & 31));
+    // the lane pair lk = 0, 1 splits the slots, four loads at a time
+    for (int k0 = lk * 4; k0 < Kn; k0 += 8) {
+      int m[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = sel_at(k0 + e);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (k0 + e >= Kn || m[e] < 0 || m[e] >= beta) continue;
+        skip_slots += (m[e] + 1) * B <= tlo * 64;
+        for (int tl = (m[e] * B) / 64; tl <= ((m[e] + 1) * B - 1) / 64; ++tl)
+          atomicOr(&need[tl >> 5], 1u << (tl & 31));
+      }
     }
   }
+  skip_slots += __shfl_xor(skip_slots, 32, 64);
   __syncthreads();
 
   floatx16_t o[DH / 32];
@@ -150,24 +147,24 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
   const bf16_t* Vg = (const bf16_t*)P.V + (size_t)g * DH;
   const size_t kstride = (size_t)P.Hkv * DH;  // elements between consecutive keys
   const size_t kbase = (size_t)bi * n;
-  const int c8 = tid % C8, kg = tid / C8;
-  // this thread's 16-byte column of keys kg * KPG + q of a tile; element
-  // offsets within the batch entry fit 32 bits (n * Hkv * DH < 2^31)
-  const bf16_t* Kb = Kg + kbase * kstride + c8 * 8;
-  const bf16_t* Vb = Vg + kbase * kstride + c8 * 8;
-  const uint32_t ks32 = (uint32_t)kstride, last_off = (uint32_t)(n - 1) * ks32;
-  u32x4_t rk[KPG], rv[KPG];  // native vectors: the staging stays in registers
+  // element offsets within the batch entry fit 32 bits (n * Hkv * DH < 2^31)
+  const bf16_t* Kb = Kg + kbase * kstride;
+  const bf16_t* Vb = Vg + kbase * kstride;
+  const uint32_t ks32 = (uint32_t)kstride;
   float r_lg[NSUB];  // full scope: this lane's log gates of the tile's blocks
-  auto prefetch = [&](int kt) {
-    // keys past the end load the last key's row instead (finite; their
-    // scores are masked and their probabilities are zero)
-    const int r0 = kt * 64 + kg * KPG;
-    const uint32_t off0 = (uint32_t)r0 * ks32;
+  // K and V rows of tile kt into buffer buf: lane's 16 bytes land at LDS piece
+  // (wave NL + i) 64 + lane, which holds chunk c of row r (see lds_chunk)
+  auto load_tile = [&](int kt, int buf) {
+    unsigned char* tb = tiles + buf * 2 * TB;
+    // keys past the end load the last key's row instead (their scores are
+    // masked and their probabilities are zero)
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) {
-      const uint32_t off = r0 + q < n ? off0 + q * ks32 : last_off;
-      rk[q] = *(const u32x4_t*)(Kb + off);
-      rv[q] = *(const u32x4_t*)(Vb + off);
+    for (int i = 0; i < NL; ++i) {
+      const int p = (wave * NL + i) * 64 + lane, r = p / C8, c = (p % C8) ^ lds_swz<DH>(r);
+      const uint32_t off = (uint32_t)min(kt * 64 + r, n - 1) * ks32 + c * 8;
+      unsigned char* d = tb + (wave * NL + i) * 1024;
+      __builtin_amdgcn_global_load_lds((const void*)(Kb + off), (attn_lds_t*)d, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)(Vb + off), (attn_lds_t*)(d + TB), 16, 0, 0);
     }
     if (full) {
 #pragma unroll
@@ -177,51 +174,43 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
       }
     }
   };
-  auto commit = [&]() {
+  // byte offsets of this lane's operands in a tile; a step or dimension block is an
+  // exclusive-or of the chunk bits: K rows lr (+ 32), chunk 2 ks + lk; V columns
+  // (transposing read) 32 dt + 16 (lane / 16 % 2) + 4 (lane % 4) .. of row
+  // 4 lk + 8 half + (lane % 16) / 4
+  uint32_t o_row = lr * DH * 2 + ((lk ^ lds_swz<DH>(lr)) << 4);
+  uint32_t o_tr[2];
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) *(u32x4_t*)(Ks + (kg * KPG + q) * KP + c8 * 8) = rk[q];
-    // V^T: word wd of a key holds dims 2 wd (low half) and 2 wd + 1; one byte
-    // permute joins the same half of two keys
-#pragma unroll
-    for (int wd = 0; wd < 4; ++wd) {
-      uint32_t a[KPG];
-#pragma unroll
-      for (int q = 0; q < KPG; ++q) a[q] = rv[q][wd];
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const uint32_t sel = hf ? 0x07060302u : 0x05040100u;
-        // dimension d = 8 c8 + e, keys kg * KPG ..: chunk c = kg * KPG / 4 (its part kg * KPG % 4)
-        const int c = (kg * KPG) >> 2;
-        bf16_t* dst = Vt + c8 * VGS + (2 * wd + hf) * VP + 16 * (c >> 2) + 8 * (c & 1) + 4 * ((c >> 1) & 1) +
-                      ((kg * KPG) & 3);
-        if constexpr (KPG == 4) {
-          *(uint2*)dst = make_uint2(__builtin_amdgcn_perm(a[1], a[0], sel), __builtin_amdgcn_perm(a[3], a[2], sel));
-        } else {
-          *(uint32_t*)dst = __builtin_amdgcn_perm(a[1], a[0], sel);
-        }
-      }
-    }
-  };
+  for (int hf = 0; hf < 2; ++hf) {
+    const int r = 4 * lk + 8 * hf + ((lane & 15) >> 2);
+    o_tr[hf] = r * DH * 2 + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ lds_swz<DH>(r)) << 4) + (lane & 1) * 8;
+  }
 
   // key tiles [tlo, thi) of this job (a part of the range when the query tile is split);
   // the selection cursor starts at the first block not consumed before tile tlo
   const int tend = min(thi, ntiles);
-  int cur = 0, next_sel = 0x7fffffff;  // selection cursor of this lane's query
-  if (Kn > 0 && qvalid) {
-    const int s0 = sel_s[qrow];
-    next_sel = s0 >= 0 ? s0 : 0x7fffffff;
-    while (next_sel != 0x7fffffff && (next_sel + 1) * B <= tlo * 64) {
-      ++cur;
-      const int s1 = cur < Kn ? sel_s[cur * 128 + qrow] : -1;
-      next_sel = s1 >= 0 ? s1 : 0x7fffffff;
+  // selection cursor of this lane's query: slot `cur` (block next_sel, log gate
+  // g_cur) and the one after it, read one slot ahead
+  int cur = skip_slots, next_sel = 0x7fffffff, s_nx = -1;
+  float g_cur = 0.f, g_nx = 0.f;
+  if (Kn > 0) {
+    const int s0 = sel_at(cur);
+    s_nx = sel_at(cur + 1);
+    if (gated) {
+      g_cur = P.sel_bias[srow + min(cur, Kn - 1)];
+      g_nx = P.sel_bias[srow + min(cur + 1, Kn - 1)];
     }
+    if (qvalid && cur < Kn && s0 >= 0) next_sel = s0;
   }
-  int kt = next_set(need, tlo, tend);
-  if (kt < tend) prefetch(kt);
+  int kt = next_set(need, tlo, tend), buf = 0;
+  if (kt < tend) load_tile(kt, 0);
   while (kt < tend) {
-    commit();
-    lds_barrier();
+    // this wave's loads of the tile are done; after the barrier everyone's are,
+    // and every wave is done with the other buffer
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int k0 = kt * 64;
+    const unsigned char* const tb = tiles + buf * 2 * TB;
+    asm volatile("" : "+v"(o_row), "+v"(o_tr[0]), "+v"(o_tr[1]));  // (formed anew per tile: kept, they would spill)
     // logit offset (log2 domain; -inf: not attended) and value weight of each sub-block
     float offs[NSUB], wts[NSUB];
 #pragma unroll
@@ -240,11 +229,13 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
         lg = r_lg[sb];
       } else if (m == next_sel) {
         att = true;
-        lg = gated ? sbias_s[cur * 128 + qrow] : 0.f;
+        lg = gated ? g_cur : 0.f;
         if (kstart + (1 << LSB) >= (m + 1) * B) {  // a block wider than a tile is consumed at its last tile
           ++cur;
-          const int s1 = cur < Kn ? sel_s[cur * 128 + qrow] : -1;
-          next_sel = s1 >= 0 ? s1 : 0x7fffffff;
+          next_sel = cur < Kn && s_nx >= 0 ? s_nx : 0x7fffffff;
+          g_cur = g_nx;
+          s_nx = sel_at(cur + 1);
+          if (gated) g_nx = P.sel_bias[srow + min(cur + 1, Kn - 1)];
         }
       }
       if (att) {
@@ -253,7 +244,7 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
       }
     }
     const int nkt = next_set(need, kt + 1, tend);
-    if (nkt < tend) prefetch(nkt);
+    if (nkt < tend) load_tile(nkt, buf ^ 1);
     // SKIP (grouped queries: a wave's 32 rows span only 32 / G positions): a
     // wave none of whose rows attends a key of the tile skips its products;
     // it still stages the tiles and meets the barriers
@@ -276,14 +267,14 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[st][v] = 0.f;
-    const bf16_t* kf = Ks + lr * KP + lk * 8;
-    bf16x8_t ka0 = *(const bf16x8_t*)kf, ka1 = *(const bf16x8_t*)(kf + 32 * KP);
+    bf16x8_t ka0 = *(const bf16x8_t*)(tb + o_row), ka1 = *(const bf16x8_t*)(tb + o_row + 32 * DH * 2);
 #pragma unroll
     for (int ks = 0; ks < DH / 16; ++ks) {
       bf16x8_t kn0 = ka0, kn1 = ka1;
       if (ks + 1 < DH / 16) {
-        kn0 = *(const bf16x8_t*)(kf + (ks + 1) * 16);
-        kn1 = *(const bf16x8_t*)(kf + 32 * KP + (ks + 1) * 16);
+        const unsigned char* kf = tb + (o_row ^ ((ks + 1) << 5));
+        kn0 = *(const bf16x8_t*)kf;
+        kn1 = *(const bf16x8_t*)(kf + 32 * DH * 2);
       }
       s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka0, qb[ks], s[0], 0, 0, 0);
       s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka1, qb[ks], s[1], 0, 0, 0);
@@ -371,14 +362,15 @@ __device__ __forceinline__ void attn_bf16_job(const AttnArgs& P, const int qtile
       const bf16x8_t pb = *(const bf16x8_t*)&pu;
 #pragma unroll
       for (int dt = 0; dt < DH / 32; ++dt) {
-        // pair 2 ks + lk of dimension dt * 32 + lr
-        const bf16_t* vr = Vt + (4 * dt + (lr >> 3)) * VGS + (lr & 7) * VP + 16 * ks + 8 * lk;
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8_t*)vr, pb, o[dt], 0, 0, 0);
+        const uint2 lo = lds_read_tr(tb + TB + (o_tr[0] ^ (dt << 6)) + ks * 16 * DH * 2);
+        const uint2 hi = lds_read_tr(tb + TB + (o_tr[1] ^ (dt << 6)) + ks * 16 * DH * 2);
+        const uint4 vu = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8_t*)&vu, pb, o[dt], 0, 0, 0);
       }
     }
     __builtin_amdgcn_s_setprio(0);
     }
-    lds_barrier();
+    buf ^= 1;
     kt = nkt;
   }
 
@@ -784,6 +776,18 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(AttnArgs P) {
   }
 }
 
+// the kernel, allowed its two tile buffers of LDS
+template <int DH, int LSB, bool OUTER, bool SKIP>
+static auto attn_kernel() {
+  static bool attr = false;
+  if (!attr) {
+    (void)hipFuncSetAttribute((const void*)attn_bf16_kernel<DH, LSB, OUTER, SKIP>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 512 * DH);
+    attr = true;
+  }
+  return attn_bf16_kernel<DH, LSB, OUTER, SKIP>;
+}
+
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
   if (a.n <= 0 || a.b <= 0) return hipSuccess;
   if (dtype == SAS_BF16) {
@@ -795,8 +799,8 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     const bool skip = a.Hkv > 0 && a.H > a.Hkv;  // grouped queries
     void (*kern)(AttnArgs, int);
 #define ATTN_PICK(DH, LSB)                                                                              \
-  kern = outer ? (skip ? attn_bf16_kernel<DH, LSB, true, true> : attn_bf16_kernel<DH, LSB, true, false>) \
-               : (skip ? attn_bf16_kernel<DH, LSB, false, true> : attn_bf16_kernel<DH, LSB, false, false>)
+  kern = outer ? (skip ? attn_kernel<DH, LSB, true, true>() : attn_kernel<DH, LSB, true, false>()) \
+               : (skip ? attn_kernel<DH, LSB, false, true>() : attn_kernel<DH, LSB, false, false>())
     if (a.dh == 128) {
       if (lsb == 6) ATTN_PICK(128, 6);
       else if (lsb == 5) ATTN_PICK(128, 5);
@@ -812,7 +816,8 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     const int qpt = 128 / (a.H / a.Hkv);
     const int nqt = cdiv(a.n, qpt), ntk = cdiv(a.n, 64), per = a.Hkv * a.b;
     const long long jobs = (long long)nqt * per;
-    const int res = resident_workgroups(kern, 256);
+    const size_t lds = (size_t)512 * a.dh;  // two buffers of K and V tiles
+    const int res = resident_workgroups(kern, 256, lds);
     if (res <= 0 || jobs > INT32_MAX) return hipErrorInvalidValue;
     AttnArgs A = a;
     A.queue = nullptr;
@@ -848,7 +853,7 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
       A.tail_units = 8;
       A.unit_group = std::min(A.unit_group, U * A.unit_parts);
     }
-    kern<<<(unsigned)std::min<long long>(total, res), 256, 0, s>>>(A, (int)total);
+    kern<<<(unsigned)std::min<long long>(total, res), 256, lds, s>>>(A, (int)total);
     if (A.split_tiles > 0) {
       const size_t rows = (size_t)a.b * a.H * a.n * (a.dh / 8);
       attn_combine_kernel<<<(unsigned)cdiv(rows, 256), 256, 0, s>>>(A);

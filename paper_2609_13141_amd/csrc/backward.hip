@@ -276,25 +276,6 @@ __global__ void fill_f32_kernel(float* p, size_t n, float v) {
 // ---- bf16 path ------------------------------------------------------------------
 constexpr float BLOG2E = 1.4426950408889634f;
 
-// LDS tiles of the two passes: rows of DH values without padding, the 16-byte
-// chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
-// (the row-major operand reads) then lie in distinct banks, and so do the four
-// rows x 32 dimensions that half a wave takes with a transposing read.
-template <int DH>
-__device__ __forceinline__ int lds_swz(int r) {
-  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
-template <int DH>
-__device__ __forceinline__ int lds_chunk(int r, int c) { return r * DH + ((c ^ lds_swz<DH>(r)) << 3); }
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-// ds_read_b64_tr_b16: in each group of 16 lanes, lane 4 j + a names 4 consecutive
-// values of row j of a 4 x 16 tile, and lane i receives column i (rows 0..3).
-__device__ __forceinline__ uint2 lds_read_tr(const unsigned char* p) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p));
-}
-
 // Pass 1 (dQ and the per-head block sums of ds): one workgroup = 4 waves =
 // 128 query rows of one batch entry and KV group, 128 / G consecutive positions x
 // the group's G heads as in the forward (the key tiles the rows attend are the

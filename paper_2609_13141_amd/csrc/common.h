@@ -40,6 +40,25 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// LDS tiles of the attention kernels: rows of DH values without padding, the 16-byte
+// chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
+// (the row-major operand reads) then lie in distinct banks, and so do the four
+// rows x 32 dimensions that half a wave takes with a transposing read.
+template <int DH>
+__device__ __forceinline__ int lds_swz(int r) {
+  return DH == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+template <int DH>
+__device__ __forceinline__ int lds_chunk(int r, int c) { return r * DH + ((c ^ lds_swz<DH>(r)) << 3); }
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+// ds_read_b64_tr_b16: in each group of 16 lanes, lane 4 j + a names 4 consecutive
+// values of row j of a 4 x 16 tile, and lane i receives column i (rows 0..3).
+__device__ __forceinline__ uint2 lds_read_tr(const unsigned char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p));
+}
+
 // next set bit at or after p in an LDS bitmask of `count` bits (count if none)
 __device__ __forceinline__ int next_set(const uint32_t* bits, int p, int count) {
   while (p < count) {
@@ -137,14 +156,14 @@ __device__ __forceinline__ int queue_next_job(uint32_t* counter) {
   return job_s;
 }
 
-// workgroups of `kernel` with `threads` threads resident on the current device
-// at once (0 when the runtime cannot tell)
+// workgroups of `kernel` with `threads` threads and `lds` bytes of dynamic LDS
+// resident on the current device at once (0 when the runtime cannot tell)
 template <typename F>
-inline int resident_workgroups(F kernel, int threads) {
+inline int resident_workgroups(F kernel, int threads, size_t lds = 0) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess) return 0;
   return cus * (per_cu > 0 ? per_cu : 1);
 }
 
