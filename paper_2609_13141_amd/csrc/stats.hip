@@ -6,7 +6,7 @@
 //
 // The coverage pass is a dense causal pass in the forward attention's layout
 // (S^T = K Q^T on v_mfma_f32_32x32x16_bf16, lane = query, partner lane l^32)
-// without the PV product: per query it keeps two running maxima (raw and
+// without the PV product: per query it keeps two running references (raw and
 // value-aware logits, log2 domain) and four sums (all keys / attended keys,
 // each weighting), and the log-sum-exp of every historical block's raw
 // logits for the reference Top-K.
@@ -46,18 +46,34 @@ __device__ __forceinline__ float lse2(float a, float b) {
   return m + log2f(exp2f(a - m) + exp2f(b - m));
 }
 
+typedef __attribute__((address_space(3))) void stats_lds_t;
+
+// Bound by VALU issue: one exponential per (query, key).  A tile's p = 2^(z - its
+// largest z) serves the raw and, times the key's value norm, the value-aware
+// sums (norms relative to the tile's largest, both references carried in the
+// log2 domain), so neither weighting needs an exponential or a maximum of its
+// own; sums are per sub-block and join the attended set's as a whole.  Where a
+// query's sum falls under 2^-60 of its reference (large logits at keys of tiny
+// values: products would leave the range of float) the wave redoes the tile's
+// value-aware sums relative to their own maximum.  K rows go straight to LDS
+// into the other of two buffers, one barrier per tile.
+// 2 x 2048 tokens, 32 heads: 97 us; with an exponential and a
+// running maximum per weighting, staged K and two barriers 162.
 template <int DH, int LSB>
 __device__ __forceinline__ void stats_bf16_job(const StatsArgs& P, const int qtile, const int h, const int bi) {
-  constexpr int KP = DH + 8;
-  constexpr int KPG = DH / 32;
   constexpr int C8 = DH / 8;
   constexpr int NSUB = 64 >> LSB;
-  constexpr int KMAX = 32;
-  __shared__ __align__(16) bf16_t Ks[64 * KP];
-  __shared__ float lv_s[64];
-  __shared__ int sel_s[128 * KMAX];
+  constexpr int TB = 64 * DH * 2;    // bytes of a K tile
+  constexpr int NL = 64 * C8 / 256;  // 16-byte pieces per thread and tile
+  constexpr int NA = NSUB == 1 ? 4 : 1;  // partial sums per sub-block
+  // two K tiles (2 TB bytes; dynamic, because the compiler makes every read of a
+  // static array wait for the direct-to-LDS loads in flight)
+  extern __shared__ __align__(16) unsigned char stats_tiles[];
+  __shared__ __align__(16) float w_s[2][64];  // value norms of the tile's keys over the largest
+  __shared__ float wmax_s[2];                 // log2 of that
+  __shared__ float lv_s[2][64];               // log2 norms themselves
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lk = lane >> 5;
   const int G = P.H / P.Hkv, g = h / G;
   const int n = P.n, B = P.B;
@@ -84,44 +100,56 @@ __device__ __forceinline__ void stats_bf16_job(const StatsArgs& P, const int qti
       qb[ks] = *(bf16x8_t*)&u;
     }
   }
-  if (Kn > 0 && qvalid)
-    for (int k = lk; k < Kn; k += 2) sel_s[qrow * KMAX + k] = P.sel[(grow + t) * Kn + k];
-  __syncthreads();
 
   const float qk_scale = P.sm_scale * SLOG2E;
   const bf16_t* Kg = (const bf16_t*)P.Kt + (size_t)g * DH;
   const size_t kstride = (size_t)P.Hkv * DH;
   const size_t kbase = (size_t)bi * n;
-  const int c8 = tid % C8, kg = tid / C8;
-  uint4 rk[KPG];
-  float rl = 0.f;
-  auto prefetch = [&](int kt) {
+  float rl = 0.f;  // wave 0: log2 norm of the next tile's key `lane`
+  auto load_tile = [&](int kt, int buf) {  // keys past the end repeat the last one (masked)
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) {
-      const int key = kt * 64 + kg * KPG + q;
-      rk[q] = key < n ? *(const uint4*)(Kg + (kbase + key) * kstride + c8 * 8) : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < NL; ++i) {
+      const int p = (wave * NL + i) * 64 + lane, r = p / C8, c = (p % C8) ^ lds_swz<DH>(r);
+      __builtin_amdgcn_global_load_lds((const void*)(Kg + (kbase + min(kt * 64 + r, n - 1)) * kstride + c * 8),
+                                       (stats_lds_t*)(stats_tiles + buf * TB + (wave * NL + i) * 1024), 16, 0, 0);
     }
-    if (tid < 64) {
-      const int key = kt * 64 + tid;
-      rl = key < n ? P.lvn[(kbase + key) * P.Hkv + g] : -INFINITY;
-    }
+    if (wave == 0) rl = P.lvn[(kbase + min(kt * 64 + lane, n - 1)) * P.Hkv + g];
   };
+  auto commit_norms = [&](int kt, int buf) {
+    if (wave != 0) return;
+    const float l = kt * 64 + lane < n ? rl : -INFINITY;
+    const float mxl = wave_max(l);
+    w_s[buf][lane] = __builtin_amdgcn_exp2f(l - (mxl == -INFINITY ? 0.f : mxl));
+    lv_s[buf][lane] = l;
+    if (lane == 0) wmax_s[buf] = mxl;
+  };
+  uint32_t o_row = lr * DH * 2 + ((lk ^ lds_swz<DH>(lr)) << 4);  // row lr, chunk 2 ks + lk: o_row ^ (ks << 5)
 
-  float m_raw = -INFINITY, m_val = -INFINITY;         // running maxima (log2 domain)
+  float m_raw = -INFINITY, m_val = -INFINITY;         // running references (log2 domain)
   float l_all = 0.f, l_S = 0.f, l_vall = 0.f, l_vS = 0.f;
   float blk_acc = -INFINITY;                           // log2 mass of a block wider than a tile so far
-  int cur = 0, next_sel = 0x7fffffff;
-  if (Kn > 0 && qvalid) {
-    const int s0 = sel_s[qrow * KMAX];
-    next_sel = s0 >= 0 ? s0 : 0x7fffffff;
+  // selection cursor: slot `cur` (block next_sel) and the one after it, read one slot ahead
+  const size_t srow = (grow + (qvalid ? t : 0)) * (size_t)Kn;
+  auto sel_at = [&](int k) -> int { return P.sel[srow + min(k, Kn - 1)]; };  // Kn > 0
+  int cur = 0, next_sel = 0x7fffffff, s_nx = -1;
+  if (Kn > 0) {
+    const int s0 = sel_at(0);
+    s_nx = sel_at(1);
+    if (qvalid && s0 >= 0) next_sel = s0;
   }
-  prefetch(first_tile);
-  for (int kt = first_tile; kt <= last_tile; ++kt) {
+  // the queries have arrived (else the compiler waits for all loads at their first
+  // use, which is in the loop)
 #pragma unroll
-    for (int q = 0; q < KPG; ++q) *(uint4*)(Ks + (kg * KPG + q) * KP + c8 * 8) = rk[q];
-    if (tid < 64) lv_s[tid] = rl;
-    lds_barrier();
+  for (int ks = 0; ks < DH / 16; ++ks) asm volatile("" : "+v"(*(u32x4_t*)&qb[ks]));
+  int buf = 0;
+  load_tile(first_tile, 0);
+  commit_norms(first_tile, 0);
+  for (int kt = first_tile; kt <= last_tile; ++kt) {
+    // this wave's loads of the tile are done; after the barrier everyone's are,
+    // and every wave is done with the other buffer
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int k0 = kt * 64;
+    const unsigned char* const tb = stats_tiles + buf * TB;
     // membership of the attended set per sub-block (causal context only)
     bool inS[NSUB], ctx[NSUB];
 #pragma unroll
@@ -137,88 +165,145 @@ __device__ __forceinline__ void stats_bf16_job(const StatsArgs& P, const int qti
         inS[sb] = true;
         if (kstart + (1 << LSB) >= (m + 1) * B) {
           ++cur;
-          const int s1 = cur < Kn ? sel_s[qrow * KMAX + cur] : -1;
-          next_sel = s1 >= 0 ? s1 : 0x7fffffff;
+          next_sel = cur < Kn && s_nx >= 0 ? s_nx : 0x7fffffff;
+          s_nx = sel_at(cur + 1);
         }
       }
     }
-    if (kt + 1 <= last_tile) prefetch(kt + 1);
+    if (kt < last_tile) load_tile(kt + 1, buf ^ 1);
 
-    floatx16_t s[2];
+    auto logits = [&](floatx16_t (&s)[2]) {
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
+      for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) s[st][v] = 0.f;
+        for (int v = 0; v < 16; ++v) s[st][v] = 0.f;
+      __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int ks = 0; ks < DH / 16; ++ks) {
-        const bf16x8_t a = *(const bf16x8_t*)(Ks + (st * 32 + lr) * KP + ks * 16 + lk * 8);
-        s[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb[ks], s[st], 0, 0, 0);
+        const unsigned char* row = tb + (o_row ^ (ks << 5));
+        const bf16x8_t a0 = *(const bf16x8_t*)row, a1 = *(const bf16x8_t*)(row + 32 * DH * 2);
+        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qb[ks], s[0], 0, 0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, qb[ks], s[1], 0, 0, 0);
       }
-    }
-    const bool diag = k0 + 63 > qtile * 128;
-    float xv[2][16];
-    float mx = -INFINITY, mxv = -INFINITY;
+      __builtin_amdgcn_s_setprio(0);
+      if (k0 + 63 > qtile * 128) {  // keys past some query of the workgroup
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+        for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int klc = st * 32 + 8 * (v >> 2);
-        const int kl = klc + 4 * lk + (v & 3);
-        float x = s[st][v] * qk_scale;
-        if (!ctx[klc >> LSB] || (diag && k0 + kl > t)) x = -INFINITY;
-        const float y = x + lv_s[kl];
-        s[st][v] = x;
-        xv[st][v] = y;
-        mx = fmaxf(mx, x);
-        mxv = fmaxf(mxv, y);
+          for (int v = 0; v < 16; ++v)
+            if (k0 + st * 32 + 8 * (v >> 2) + 4 * lk + (v & 3) > t) s[st][v] = -INFINITY;
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    mxv = fmaxf(mxv, __shfl_xor(mxv, 32, 64));
-    const float mn = fmaxf(m_raw, mx), mnv = fmaxf(m_val, mxv);
-    const float mu = mn == -INFINITY ? 0.f : mn, muv = mnv == -INFINITY ? 0.f : mnv;
-    const float a = exp2f(m_raw - mu), av = exp2f(m_val - muv);
-    float sa = 0.f, sS = 0.f, sva = 0.f, svS = 0.f, bsum[NSUB];
+    };
+    floatx16_t s[2];
+    logits(s);
+    // the tile's largest logit (the scale is positive: per sub-block the largest raw score)
+    float mxs[NSUB];
 #pragma unroll
-    for (int sb = 0; sb < NSUB; ++sb) bsum[sb] = 0.f;
+    for (int sb = 0; sb < NSUB; ++sb) mxs[sb] = -INFINITY;
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int sb = (st * 32 + 8 * (v >> 2)) >> LSB;
-        const float p = exp2f(s[st][v] - mu);
-        const float pv = exp2f(xv[st][v] - muv);
-        sa += p;
-        sva += pv;
-        bsum[sb] += p;
-        if (inS[sb]) {
-          sS += p;
-          svS += pv;
+        mxs[sb] = fmaxf(mxs[sb], s[st][v]);
+      }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) mx = fmaxf(mx, ctx[sb] ? mxs[sb] * qk_scale : -INFINITY);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float ref = mx == -INFINITY ? 0.f : mx;
+    float bs[NSUB][NA], vs[NSUB][NA];
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb)
+#pragma unroll
+      for (int i = 0; i < NA; ++i) bs[sb][i] = vs[sb][i] = 0.f;
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int sb = (st * 32 + 8 * j) >> LSB;
+        const float4 w4 = *(const float4*)&w_s[buf][st * 32 + 8 * j + 4 * lk];
+        const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[st][4 * j + i], qk_scale, -ref));
+          bs[sb][i % NA] += p;
+          vs[sb][i % NA] = fmaf(p, w[i], vs[sb][i % NA]);
         }
       }
-    sa += __shfl_xor(sa, 32, 64);
-    sS += __shfl_xor(sS, 32, 64);
-    sva += __shfl_xor(sva, 32, 64);
-    svS += __shfl_xor(svS, 32, 64);
-    l_all = l_all * a + sa;
-    l_S = l_S * a + sS;
-    l_vall = l_vall * av + sva;
-    l_vS = l_vS * av + svS;
+    float sa = 0.f, sS = 0.f, sva = 0.f, svS = 0.f, bsum[NSUB];
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) {
+      float x = bs[sb][0], y = vs[sb][0];
+#pragma unroll
+      for (int i = 1; i < NA; ++i) {
+        x += bs[sb][i];
+        y += vs[sb][i];
+      }
+      x += __shfl_xor(x, 32, 64);
+      y += __shfl_xor(y, 32, 64);
+      if (!ctx[sb]) x = y = 0.f;  // whatever these keys hold
+      bsum[sb] = x;
+      sa += x;
+      sva += y;
+      if (inS[sb]) {
+        sS += x;
+        svS += y;
+      }
+    }
+    // join the running sums: raw reference mx, value-aware mx + log2 of the largest norm
+    const float wmax = wmax_s[buf];
+    float mxv = wmax == -INFINITY ? -INFINITY : mx + wmax;
+    if (__any(sva < 0x1p-60f && mxv > -INFINITY)) {
+      floatx16_t z[2];
+      logits(z);
+      mxv = -INFINITY;
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          z[st][v] = ctx[(st * 32 + 8 * (v >> 2)) >> LSB]
+                         ? fmaf(z[st][v], qk_scale, lv_s[buf][st * 32 + 8 * (v >> 2) + 4 * lk + (v & 3)]) : -INFINITY;
+          mxv = fmaxf(mxv, z[st][v]);
+        }
+      mxv = fmaxf(mxv, __shfl_xor(mxv, 32, 64));
+      const float zr = mxv == -INFINITY ? 0.f : mxv;
+      sva = svS = 0.f;
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float p = __builtin_amdgcn_exp2f(z[st][v] - zr);
+          sva += p;
+          if (inS[(st * 32 + 8 * (v >> 2)) >> LSB]) svS += p;
+        }
+      sva += __shfl_xor(sva, 32, 64);
+      svS += __shfl_xor(svS, 32, 64);
+    }
+    const float mn = fmaxf(m_raw, mx), mnv = fmaxf(m_val, mxv);
+    const float mu = mn == -INFINITY ? 0.f : mn, muv = mnv == -INFINITY ? 0.f : mnv;
+    const float a = __builtin_amdgcn_exp2f(m_raw - mu), c = __builtin_amdgcn_exp2f(mx - mu);
+    const float av = __builtin_amdgcn_exp2f(m_val - muv), cv = __builtin_amdgcn_exp2f(mxv - muv);
+    l_all = l_all * a + sa * c;
+    l_S = l_S * a + sS * c;
+    l_vall = l_vall * av + sva * cv;
+    l_vS = l_vS * av + svS * cv;
     m_raw = mn;
     m_val = mnv;
     // block masses of the historical blocks (reference Top-K)
 #pragma unroll
     for (int sb = 0; sb < NSUB; ++sb) {
-      const float tot = bsum[sb] + __shfl_xor(bsum[sb], 32, 64);
       const int kstart = k0 + (sb << LSB), m = kstart / B;
       if (P.blk_lse && lk == 0 && ctx[sb] && m < beta) {
-        blk_acc = lse2(blk_acc, tot > 0.f ? mu + log2f(tot) : -INFINITY);
+        blk_acc = lse2(blk_acc, bsum[sb] > 0.f ? ref + log2f(bsum[sb]) : -INFINITY);
         if (kstart + (1 << LSB) >= (m + 1) * B) {
           P.blk_lse[hrow * NB + m] = blk_acc;
           blk_acc = -INFINITY;
         }
       }
     }
-    lds_barrier();
+    buf ^= 1;
+    if (kt < last_tile) commit_norms(kt + 1, buf);
   }
   if (!qvalid || lk != 0) return;
   if (P.cov) P.cov[hrow] = l_S / l_all;
@@ -235,6 +320,7 @@ __global__ void __launch_bounds__(256, 2) stats_bf16_kernel(StatsArgs P) {
     const int job = P.queue ? queue_next_job(P.queue) : (it == 0 ? (int)blockIdx.x : njobs);
     if (job >= njobs) break;
     const int r = job % per;
+    __syncthreads();  // the previous job is done with LDS
     stats_bf16_job<DH, LSB>(P, nqt - 1 - job / per, r % P.H, r / P.H);
   }
 }
@@ -444,7 +530,8 @@ hipError_t launch_stats(int dtype, const StatsArgs& a, hipStream_t s) {
                           : (lsb == 6 ? stats_bf16_kernel<64, 6> : lsb == 5 ? stats_bf16_kernel<64, 5>
                                                                              : stats_bf16_kernel<64, 4>);
   const long long jobs = (long long)cdiv(a.n, 128) * a.H * a.b;
-  const int res = resident_workgroups(kern, 256);
+  const size_t lds = (size_t)256 * a.dh;  // two K tiles (at most 32 KB)
+  const int res = resident_workgroups(kern, 256, lds);
   if (res <= 0 || jobs > INT32_MAX) return hipErrorInvalidValue;
   StatsArgs A = a;
   A.queue = nullptr;
@@ -454,7 +541,7 @@ hipError_t launch_stats(int dtype, const StatsArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     A.queue = a.queue;
   }
-  kern<<<(unsigned)std::min<long long>(jobs, res), 256, 0, s>>>(A);
+  kern<<<(unsigned)std::min<long long>(jobs, res), 256, lds, s>>>(A);
   return hipGetLastError();
 }
 
