@@ -1,13 +1,16 @@
 """Selection statistics at the edges of the bf16 pass: ragged lengths, every
-sub-block width, grouped queries, several documents, value norms that span
-many magnitudes (the sums' references change from tile to tile, products of
-weight and norm leave the range of float) and logits far apart; against the fp64 oracle."""
+sub-block width, grouped queries, value norms that span many magnitudes (the
+sums' references change from tile to tile, products of weight and norm leave
+the range of float) and logits far apart, and the reference Top-K's list sizes,
+words and ties; against the fp64 oracle."""
 import numpy as np
 import pytest
 
+from oracle.stats import block_mass_topk, majority_vote
 from paper_2609_13141_amd import configs, inputs, sas
 
 from helpers import assert_close, f64
+from test_gpu_stats import _bits, _clear_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +49,27 @@ def test_coverage(n, H, Hkv, dh, B, K, norms, logits):
             cov[t], cov_v[t] = p[keep].sum() / p.sum(), (p * vn[:t + 1])[keep].sum() / (p * vn[:t + 1]).sum()
         assert_close(out["cov"][0, h].cpu().numpy(), cov, "f32", f"cov {h}", tol=tol)
         assert_close(out["cov_v"][0, h].cpu().numpy(), cov_v, "f32", f"cov_v {h}", tol=tol)
+
+
+@pytest.mark.parametrize("n,B,K", [(700, 16, 8), (700, 16, 9), (1200, 16, 32), (600, 64, 16), (100, 64, 4)])
+def test_reference_topk(n, B, K):
+    print(f"\n[case] reference Top-K n={n} B={B} K={K}", flush=True)
+    w = configs.L7B_1K.with_(seq_len=n, n_heads=2, n_kv_heads=2, head_dim=64, block_size=B, top_k=K,
+                             segments=(("txt", n),), index=128)
+    q, k, v = inputs.qkv(w)
+    cfg = sas.make_config(w, "gated")
+    NB = -(-n // B)
+    for zero in (False, True):
+        dq, dk, dv = (sas.to_device(a, "bf16") for a in (q * 0 if zero else q, k, v))
+        sel = sas.attention_prefill(cfg, dq, dk, dv)["sel_idx"]
+        ru = sas.alloc_union(cfg, 1, n)
+        sas.selection_stats(cfg, dq, dk, dv, sel, ref_union=ru)
+        got = _bits(ru, NB)[0]
+        if zero:  # every block's mass is the same: the lower blocks win
+            want = np.arange(NB)[None] < np.minimum(K, np.arange(n) // B)[:, None]
+            np.testing.assert_array_equal(got, np.stack([want, want]))
+            continue
+        hs, lmass = block_mass_topk(f64(q[0]), f64(k[0]), B, K)
+        ok = _clear_rows(lmass, K, 1)
+        assert ok.mean() > 0.9
+        np.testing.assert_array_equal(got[ok], majority_vote(hs, 1)[ok])
