@@ -280,7 +280,7 @@ constexpr float BLOG2E = 1.4426950408889634f;
 // 128 query rows of one batch entry and KV group, 128 / G consecutive positions x
 // the group's G heads as in the forward (the key tiles the rows attend are the
 // union over the positions only); a wave none of whose rows attends a key of
-// the tile skips its products (SKIP, grouped queries).  Each lane owns one query
+// the tile or takes a gradient from it skips it (SKIP, grouped queries).  Each lane owns one query
 // of S^T = K Q^T (v_mfma_f32_32x32x16_bf16), with dP^T = V dO^T computed the
 // same way; dS^T = P^T (dP^T - Delta) is formed in registers and fed back as the
 // B operand of dQ^T += K^T dS^T, whose A operand is read from the same K rows
@@ -452,7 +452,7 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
     asm volatile("" : "+v"(o_row), "+v"(o_tr[0]), "+v"(o_tr[1]));  // (formed anew per tile: kept, they would spill)
 
     // per sub-block: offset (log2-domain bias - LSE; -inf: neither attended nor
-    // receiving a gradient), value weight, attended, selection slot
+    // receiving a gradient, or a zero gate), value weight, attended, selection slot
     float offs[NSUB], wts[NSUB];
     bool attb[NSUB], gradb[NSUB];
     int slot[NSUB];
@@ -500,10 +500,11 @@ __device__ __forceinline__ void bwd_dq_bf16_job(const BwdArgs& P, const int qtil
     const int nkt = next_set(need, kt + 1, ntiles);
     if (nkt < ntiles) prefetch(nkt);
 
+    // a block with a zero gate (its offset is -inf) counts: its block sum, 0, is written below
     bool any = !SKIP;
     if constexpr (SKIP) {
 #pragma unroll
-      for (int sb = 0; sb < NSUB; ++sb) any = any || offs[sb] != -INFINITY;
+      for (int sb = 0; sb < NSUB; ++sb) any = any || attb[sb] || gradb[sb];
     }
     if (!SKIP || __builtin_amdgcn_ballot_w64(any) != 0) {
     const bool diag = k0 + 63 > t0;  // keys past some query of the workgroup: mask key > t
