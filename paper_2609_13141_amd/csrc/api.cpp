@@ -606,7 +606,10 @@ struct SelBwdWs {
   void* qhat;
   float* ds;
   float* dkbar;
-  float* s1;    // sum_t ds[t, m] qhat0[t] (for dW_gq)
+  float* s1;       // sum_t ds[t, m] qhat0[t] (for dW_gq)
+  float* row_sum;  // sum_m ds[t, m] (for dW_gq, softmax)
+  float* shift;    // mean of kbar, and its weight in dW_gq (softmax)
+  float* shift_w;
   float* part;
 };
 
@@ -636,6 +639,9 @@ SelBwdWs carve_selector_backward(Carve& cv, const sas_config* c, int b, int n) {
   w.ds = (float*)cv.take((size_t)b * Hkv * n * h.NB * 4);
   w.dkbar = (float*)cv.take((size_t)b * Hkv * h.NB * dh * 4);
   w.s1 = (float*)cv.take((size_t)b * Hkv * h.NB * dh * 4);
+  w.row_sum = (float*)cv.take((size_t)b * Hkv * n * 4);
+  w.shift = (float*)cv.take((size_t)b * Hkv * dh * 4);
+  w.shift_w = (float*)cv.take((size_t)b * Hkv * dh * 4);
   w.part = (float*)cv.take(2 * h.part_floats * 4);
   return w;
 }
@@ -951,11 +957,13 @@ sas_status sas_selector_backward(const sas_config* c, int32_t batch, int32_t seq
     HIP_TRY(launch_gate_query(c->dtype, in->q, batch, n, H, Hkv, dh, in->w_gq, w.qplain, w.qhat, s), "gate query");
   }
   float* ds = out->ds ? out->ds : w.ds;
+  const int act = gated_of(c) ? c->gate_act : SAS_ACT_SOFTMAX;
+  // softmax: the rows of ds add to zero, so a part that all summaries share cancels out of dW_gq
+  const bool shifted = dw_gq && act == SAS_ACT_SOFTMAX;
   {
     Timed tm("sel_bwd_ds", s);
-    HIP_TRY(launch_selector_ds(slots ? in->sel_idx : nullptr, in->log_gate, in->dlog_gate, dfull,
-                               gated_of(c) ? c->gate_act : SAS_ACT_SOFTMAX, batch, n, Hkv, slots ? K : 0, B, ds,
-                               in->doc_first_block, s),
+    HIP_TRY(launch_selector_ds(slots ? in->sel_idx : nullptr, in->log_gate, in->dlog_gate, dfull, act, batch, n, Hkv,
+                               slots ? K : 0, B, ds, shifted ? w.row_sum : nullptr, in->doc_first_block, s),
             "ds");
   }
   // s = r / (G sqrt(dh)) with r = qhat . kbar
@@ -990,21 +998,36 @@ sas_status sas_selector_backward(const sas_config* c, int32_t batch, int32_t seq
         HIP_TRY(launch_partial_sum(g.C[i], 1, h.Z, h.splits, E, dst[i], s), "dkbar sum");
   }
   const size_t E = (size_t)dh * dh;
-  auto dw = [&](const float* a, const void* bm, long long ci, long long cj, float* out_dw) -> hipError_t {
+  auto dw = [&](const float* a, const void* bm, long long ci, long long cj, bool shift, float* out_dw) -> hipError_t {
     // dW[g] = sum_b sum_m of products of row m of `a` and of `bm`
     SmallGemm g = {};
     g.M = dh, g.N = dh, g.K = NB, g.Z = h.Z, g.splits = 1, g.nmat = 1, g.alpha = 1.f;
     g.A = a, g.sAz = (long long)NB * dh, g.sAi = 1, g.sAk = dh;
     g.Bm[0] = bm, g.sBz = (long long)NB * dh, g.sBk = dh;
     g.C[0] = batch == 1 ? out_dw : w.part, g.sCz = (long long)E, g.sCi = ci, g.sCj = cj;
+    if (shift) g.shift = w.shift, g.shift_w = w.shift_w;
     const hipError_t e = launch_small_gemm(c->dtype, g, s);
     if (e != hipSuccess || batch == 1) return e;
     return launch_partial_sum(w.part, batch, Hkv, 1, E, out_dw, s);
   };
-  // dW_gq[k, j] = sum_t dqhat[t, k] qhat0[t, j] = sum_m kbar[m, k] s1[m, j]: NB terms instead of n
-  if (dw_gq) HIP_TRY(dw(w.s1, w.ksum, 1, dh, dw_gq), "dw_gq");
+  // dW_gq[k, j] = sum_t dqhat[t, k] qhat0[t, j] = sum_m kbar[m, k] s1[m, j]: NB terms instead of n.
+  // For the softmax gate sum_m s1[m] is zero but for the rounding of ds, and a mean of kbar many
+  // times its spread would multiply the rounding of s1 instead: it is subtracted first, and its
+  // share is added back with the rows' own sums, sum_t (sum_m ds[t, m]) qhat0[t], which cancel
+  // row by row.  Error against 64 bits with a mean of 40 times the spread, 4096 rows, 64 blocks:
+  // 6e-6 of the largest value, as in the order over dqhat; without the shift 2.7e-5.
+  if (shifted) {
+    SelShift a = {};
+    a.Z = h.Z, a.n = n, a.dh = dh, a.NB = NB, a.nf = n / B, a.alpha = dr_scale;
+    // enough workgroups to fill the chip, at least 256 rows each; dh parts fit the scratch of dW
+    a.splits = std::max(1, std::min({cdiv(1024, h.Z), cdiv(n, 256), dh}));
+    a.q = w.qplain, a.kbar = w.ksum, a.row_sum = w.row_sum;
+    a.part = w.part, a.shift = w.shift, a.shift_w = w.shift_w;
+    HIP_TRY(launch_selector_shift(c->dtype, a, s), "summary mean");
+  }
+  if (dw_gq) HIP_TRY(dw(w.s1, w.ksum, 1, dh, shifted, dw_gq), "dw_gq");
   // dW_gk[k, j] = sum_m dkbar[m, k] kbar0[m, j]
-  if (dw_gk) HIP_TRY(dw(dkbar, w.kplain, dh, 1, dw_gk), "dw_gk");
+  if (dw_gk) HIP_TRY(dw(dkbar, w.kplain, dh, 1, false, dw_gk), "dw_gk");
   return SAS_OK;
 }
 

@@ -1212,7 +1212,8 @@ __global__ void __launch_bounds__(256) selector_ds_kernel(const int32_t* __restr
                                                           const float* __restrict__ dlog_gate,
                                                           const float* __restrict__ dfull, int act, int rows,
                                                           int n, int Hkv, int K, int B, int NB,
-                                                          float* __restrict__ ds, const int32_t* __restrict__ doc) {
+                                                          float* __restrict__ ds, float* __restrict__ row_sum,
+                                                          const int32_t* __restrict__ doc) {
   __shared__ float slot_s[4][DS_ROWS][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = ((int)blockIdx.x * 4 + wave) * DS_ROWS;
@@ -1245,6 +1246,9 @@ __global__ void __launch_bounds__(256) selector_ds_kernel(const int32_t* __restr
       D[r] = wave_sum(d);
     }
   }
+  float total[DS_ROWS];
+#pragma unroll
+  for (int r = 0; r < DS_ROWS; ++r) total[r] = 0.f;
   for (int m0 = 0; m0 < NB; m0 += 64) {
     const int m = m0 + lane;
     float dl[DS_ROWS], lg[DS_ROWS];
@@ -1275,19 +1279,26 @@ __global__ void __launch_bounds__(256) selector_ds_kernel(const int32_t* __restr
         else v = dl[r];
       }
       if (m < NB && row0 + r < rows) ds[(size_t)(row0 + r) * NB + m] = v;
+      total[r] += v;
     }
+  }
+  if (!row_sum) return;
+#pragma unroll
+  for (int r = 0; r < DS_ROWS; ++r) {
+    const float sum = wave_sum(total[r]);
+    if (lane == 0 && row0 + r < rows) row_sum[row0 + r] = sum;
   }
 }
 
 hipError_t launch_selector_ds(const int32_t* sel, const float* log_gate, const float* dlog_gate,
                               const float* dlog_gate_full, int act, int b, int n, int Hkv, int K, int B, float* ds,
-                              const int32_t* doc, hipStream_t s) {
+                              float* row_sum, const int32_t* doc, hipStream_t s) {
   const int rows = b * Hkv * n;
   if (rows <= 0) return hipSuccess;
   if (K > 64) return hipErrorInvalidValue;
   if (K > 0 && !dlog_gate_full && (!sel || !dlog_gate)) return hipErrorInvalidValue;
   selector_ds_kernel<<<cdiv(rows, 4 * DS_ROWS), 256, 0, s>>>(sel, log_gate, dlog_gate, dlog_gate_full, act, rows, n,
-                                                             Hkv, K, B, cdiv(n, B), ds, doc);
+                                                             Hkv, K, B, cdiv(n, B), ds, row_sum, doc);
   return hipGetLastError();
 }
 
@@ -1299,7 +1310,7 @@ hipError_t launch_selector_ds(const int32_t* sel, const float* log_gate, const f
 // registers during this one.  Loads of A run along its contiguous index.
 // ds^T [qhat0 | qhat], 4 x 4096 rows, 32 groups, 64 blocks, dh = 128: 179 us
 // for both (17 GFLOP); the VALU tile it replaces took 211 us for one.
-template <typename T, int DH>
+template <typename T, int DH, bool SHIFT>
 __global__ void __launch_bounds__(256) small_gemm_kernel(SmallGemm P) {
   constexpr int AP = 97, BP = DH + 32, TN = DH / 2, FN = TN / 32, NB8 = 32 * (DH / 8) / 256;
   __shared__ float As[32 * AP];
@@ -1321,6 +1332,12 @@ __global__ void __launch_bounds__(256) small_gemm_kernel(SmallGemm P) {
   for (int f = 0; f < FN; ++f)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+  float sh[8];  // this thread's columns of the shift (256 is a multiple of DH / 8)
+  if constexpr (SHIFT) {
+    const float* sp8 = P.shift + (size_t)z * DH + (tid % (DH / 8)) * 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sh[j] = sp8[j];
+  }
   float ra[8];
   Vec8<T> rb[NB8];
   auto load = [&](int k0) {
@@ -1350,7 +1367,7 @@ __global__ void __launch_bounds__(256) small_gemm_kernel(SmallGemm P) {
       const bool in = k0 + idx / (DH / 8) < ke;  // (a repeated row may hold an infinity)
       float x[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = in ? rb[e].get(j) : 0.f;
+      for (int j = 0; j < 8; ++j) x[j] = in ? (SHIFT ? rb[e].get(j) - sh[j] : rb[e].get(j)) : 0.f;
       *(float4*)d = make_float4(x[0], x[1], x[2], x[3]);
       *(float4*)(d + 4) = make_float4(x[4], x[5], x[6], x[7]);
     }
@@ -1374,7 +1391,10 @@ __global__ void __launch_bounds__(256) small_gemm_kernel(SmallGemm P) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * lk + (v & 3), j = wj * TN + f * 32 + lr;
-      if (i < P.M) C[i * P.sCi + j * P.sCj] = P.alpha * acc[f][v];
+      if (i >= P.M) continue;
+      float y = P.alpha * acc[f][v];
+      if constexpr (SHIFT) y = fmaf(P.shift_w[(size_t)z * P.M + i], P.shift[(size_t)z * DH + j], y);
+      C[i * P.sCi + j * P.sCj] = y;
     }
 }
 
@@ -1383,13 +1403,84 @@ hipError_t launch_small_gemm(int dtype, const SmallGemm& g, hipStream_t s) {
   if (g.splits < 1 || (g.N != 64 && g.N != 128) || (g.sAi != 1 && g.sAk != 1) || g.nmat < 1 || g.nmat > 2)
     return hipErrorInvalidValue;
   if ((size_t)g.Z * g.splits > 65535) return hipErrorInvalidValue;
+  if (g.shift && (!g.shift_w || g.splits != 1 || g.nmat != 1)) return hipErrorInvalidValue;
   dim3 grid(cdiv(g.M, 64), g.nmat, g.Z * g.splits);
+  auto run = [&](auto kern) { kern<<<grid, 256, 0, s>>>(g); };
   if (dtype == SAS_BF16) {
-    if (g.N == 128) small_gemm_kernel<bf16_t, 128><<<grid, 256, 0, s>>>(g);
-    else small_gemm_kernel<bf16_t, 64><<<grid, 256, 0, s>>>(g);
+    if (g.N == 128) run(g.shift ? small_gemm_kernel<bf16_t, 128, true> : small_gemm_kernel<bf16_t, 128, false>);
+    else run(g.shift ? small_gemm_kernel<bf16_t, 64, true> : small_gemm_kernel<bf16_t, 64, false>);
   } else {
-    if (g.N == 128) small_gemm_kernel<float, 128><<<grid, 256, 0, s>>>(g);
-    else small_gemm_kernel<float, 64><<<grid, 256, 0, s>>>(g);
+    if (g.N == 128) run(g.shift ? small_gemm_kernel<float, 128, true> : small_gemm_kernel<float, 128, false>);
+    else run(g.shift ? small_gemm_kernel<float, 64, true> : small_gemm_kernel<float, 64, false>);
+  }
+  return hipGetLastError();
+}
+
+// part[z, split, j] = alpha sum_{t in split} w[z, t] x[z, t, j]; bound by reading x.
+// 16 or 32 rows at a time, 8 columns per thread, the rows' sums added in LDS.
+template <typename T, int DH>
+__global__ void __launch_bounds__(256) weighted_rows_kernel(const T* __restrict__ x, const float* __restrict__ w, int n,
+                                                            int splits, float alpha, float* __restrict__ part) {
+  constexpr int C8 = DH / 8, R = 256 / C8;
+  __shared__ float sum_s[R][DH + 4];
+  const int tid = threadIdx.x, c8 = tid % C8, r = tid / C8;
+  const int z = blockIdx.x / splits, sp = blockIdx.x % splits, per = (n + splits - 1) / splits;
+  const int t1 = min(n, (sp + 1) * per);
+  float acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+  for (int t = sp * per + r; t < t1; t += R) {
+    const float wt = w[(size_t)z * n + t];
+    Vec8<T> v;
+    v.load(x + ((size_t)z * n + t) * DH + c8 * 8);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = fmaf(wt, v.get(j), acc[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) sum_s[r][c8 * 8 + j] = acc[j];
+  __syncthreads();
+  if (tid >= DH) return;
+  float s = 0.f;
+  for (int q = 0; q < R; ++q) s += sum_s[q][tid];
+  part[(size_t)blockIdx.x * DH + tid] = alpha * s;
+}
+
+// shift[z, j] = mean of the first nf rows of x[z, nb, DH] (fp64 sums), and
+// shift_w[z, j] = sum over the splits of part[z, split, j]
+template <typename T, int DH>
+__global__ void __launch_bounds__(256) shift_kernel(const T* __restrict__ x, int nb, int nf, int splits,
+                                                    const float* __restrict__ part, float* __restrict__ shift,
+                                                    float* __restrict__ shift_w) {
+  constexpr int R = 256 / DH;
+  __shared__ double sum_s[R][DH];
+  const int tid = threadIdx.x, j = tid % DH, r = tid / DH, z = blockIdx.x;
+  double s = 0.0;
+  for (int m = r; m < nf; m += R) s += (double)Act<T>::to_f32(x[((size_t)z * nb + m) * DH + j]);
+  sum_s[r][j] = s;
+  __syncthreads();
+  if (r != 0) return;
+  for (int q = 1; q < R; ++q) s += sum_s[q][j];
+  shift[(size_t)z * DH + j] = nf > 0 ? (float)(s / (double)nf) : 0.f;
+  float p = 0.f;
+  for (int q = 0; q < splits; ++q) p += part[((size_t)z * splits + q) * DH + j];
+  shift_w[(size_t)z * DH + j] = p;
+}
+
+template <typename T, int DH>
+static void run_selector_shift(const SelShift& a, hipStream_t s) {
+  weighted_rows_kernel<T, DH><<<(unsigned)a.Z * a.splits, 256, 0, s>>>((const T*)a.q, a.row_sum, a.n, a.splits, a.alpha,
+                                                                      a.part);
+  shift_kernel<T, DH><<<a.Z, 256, 0, s>>>((const T*)a.kbar, a.NB, a.nf, a.splits, a.part, a.shift, a.shift_w);
+}
+
+hipError_t launch_selector_shift(int dtype, const SelShift& a, hipStream_t s) {
+  if (a.Z <= 0 || a.n <= 0 || a.splits < 1) return hipErrorInvalidValue;
+  if (dtype == SAS_BF16) {
+    if (a.dh == 128) run_selector_shift<bf16_t, 128>(a, s);
+    else run_selector_shift<bf16_t, 64>(a, s);
+  } else {
+    if (a.dh == 128) run_selector_shift<float, 128>(a, s);
+    else run_selector_shift<float, 64>(a, s);
   }
   return hipGetLastError();
 }

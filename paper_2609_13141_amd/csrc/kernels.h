@@ -259,16 +259,19 @@ hipError_t launch_gather_gate(const int32_t* sel, const float* log_gate, int b, 
 // Selector backward.  ds[r, m] for rows r = (b, g, t), m < NB, from the log-gate
 // gradient dl (per slot: dlog_gate at the slots of sel; or the full table):
 // SOFTMAX dl_m - exp(log_gate[r, m]) sum_m' dl_m'; SIGMOID dl_m (1 - exp(log_gate));
-// RAW dl_m; for m < t / B (the row's historical blocks), 0 otherwise.
+// RAW dl_m; for m < t / B (the row's historical blocks), 0 otherwise.  row_sum
+// [rows] (or null): the sum of each row's ds.
 hipError_t launch_selector_ds(const int32_t* sel, const float* log_gate, const float* dlog_gate,
                               const float* dlog_gate_full, int act, int b, int n, int Hkv, int K, int B, float* ds,
-                              const int32_t* doc, hipStream_t s);
+                              float* row_sum, const int32_t* doc, hipStream_t s);
 // C(mat, z, split)[i, j] = alpha sum_{k in split} A(z)[i, k] B(mat, z)[k, j] for
 // mat < nmat, z < Z, j < N = 64 or 128: fp32 A with sAi = 1 or sAk = 1, B of the
 // activation dtype with rows of N values, fp32 C; strides in elements.  With
 // splits > 1 each split writes its own partial at C + split * sCs.  kmin_b > 0:
 // A[i, k] is zero for k < (i + 1) kmin_b; kmax_b > 0: zero for k >= i / kmax_b
-// (the parts of ds that no row reaches are not read).
+// (the parts of ds that no row reaches are not read).  With `shift` [Z, N] (one
+// matrix, one split) the product is alpha sum_k A[i, k] (B[k, j] - shift[j]) +
+// shift_w[i] shift[j], shift_w [Z, M].
 struct SmallGemm {
   int M, N, K, Z, splits, nmat;
   float alpha;
@@ -279,8 +282,20 @@ struct SmallGemm {
   float* C[2];
   long long sCz, sCs, sCi, sCj;
   int kmin_b, kmax_b;
+  const float *shift, *shift_w;
 };
 hipError_t launch_small_gemm(int dtype, const SmallGemm& g, hipStream_t s);
+// The common part of the block summaries and its weight in dW_gq: shift[z] = the
+// mean of the complete blocks' kbar[z, m], shift_w[z] = alpha sum_t row_sum[z, t]
+// q[z, t].  `part`: Z splits dh floats of scratch.
+struct SelShift {
+  int Z, n, dh, NB, nf, splits;
+  float alpha;
+  const void *q, *kbar;  // [Z, n, dh], [Z, NB, dh] (activation dtype)
+  const float* row_sum;  // [Z, n]
+  float *part, *shift, *shift_w;
+};
+hipError_t launch_selector_shift(int dtype, const SelShift& a, hipStream_t s);
 // out[zo, e] = sum_{u < U} sum_{q < S} part[((u ZO + zo) S + q) E + e]
 hipError_t launch_partial_sum(const float* part, int U, int ZO, int S, size_t E, float* out, hipStream_t s);
 

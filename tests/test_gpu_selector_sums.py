@@ -67,3 +67,41 @@ def test_selector_products(dtype, b, n, H, Hkv, dh, B, K, proj):
         for name, want in dw.items():
             assert_close(full[name].cpu().numpy(), want, "f32", name)
             assert torch.equal(full[name], few[name])
+
+
+@pytest.mark.parametrize("n,B,K,full", [(4096, 64, 16, False), (1100, 16, 8, True)])
+def test_projection_gradient_of_keys_with_a_common_part(n, B, K, full):
+    """Summaries that share a component many times their spread: the rows of ds
+    add to zero, so the common part cancels out of dW_gq, and has to cancel
+    before fp32 sums over the rows round it (the bound of this file; about 6e-6
+    when it cancels row by row, 3e-5 when only the last sum over blocks does)."""
+    print(f"\n[case] selector sums with offset n={n} B={B} K={K} full={full}", flush=True)
+    dh = 128
+    w = configs.TINY.with_(dtype="bf16", seq_len=n, n_heads=1, n_kv_heads=1, head_dim=dh, block_size=B, top_k=K,
+                           segments=(("txt", n),), index=127)
+    q, k, v = inputs.qkv(w)
+    off = inputs.normal(w, "offset", (dh,), 40.0 / math.sqrt(B), dtype="f32")  # 40 times the summaries' spread
+    k = (k + off).astype(np.float32)
+    wgq = (np.eye(dh) + inputs.normal(w, "w_gq", (1, dh, dh), 0.02)).astype(np.float32)
+    dev = [sas.to_device(a, "bf16") for a in (q, k, v, wgq)]
+    cfg = sas.make_config(w, "gated", scope="full" if full else "sparse")
+    f = sas.attention_prefill(cfg, *dev, log_gate=True)
+    NB, nf = -(-n // B), n // B
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    dlg = torch.randn(1, 1, n, NB if full else K, generator=gen, device="cuda")
+    got = sas.selector_backward(cfg, dev[0], dev[1], f["sel_idx"], f["log_gate"], None if full else dlg, dev[3], None,
+                                ds=False, dqhat=False, dkbar=False, dlog_gate_full=dlg if full else None)
+    lg = f["log_gate"][0, 0].double().cpu()
+    hist = torch.isfinite(lg)
+    if full:
+        dl = torch.where(hist, dlg[0, 0].double().cpu(), 0.0)
+    else:
+        sel = f["sel_idx"][0, 0].long().cpu()
+        dl = torch.zeros(n, NB + 1, dtype=torch.float64)
+        dl.scatter_(1, torch.where(sel >= 0, sel, NB), dlg[0, 0].double().cpu())
+        dl = dl[:, :NB]
+    ds = torch.where(hist, dl - lg.exp() * dl.sum(1, keepdim=True), 0.0)[:, :nf]
+    q0 = torch.from_numpy(q[0, :, 0]).double()
+    kb = f["k_summary"][0, 0, :nf].double().cpu()
+    want = ((ds @ kb).T @ q0) / math.sqrt(dh)
+    assert_close(got["dw_gq"][0].cpu().numpy(), want.numpy(), "f32", "dw_gq")
