@@ -584,15 +584,16 @@ gemm_bf16_lds_kernel(GemmParams P) {
   const int m0 = mt * BM, n0 = nt * BN;
 
   // per-lane sources of the direct-to-LDS loads (rows clamped; results of
-  // clamped rows are never stored)
+  // clamped rows are never stored); A's offsets count from the tile's first row,
+  // so that they fit 32 bits for any number of rows
+  const bf16_t* const a_tile = P.A + (size_t)m0 * P.K;
   uint32_t a_off[AI];
   const bf16_t* b_src[BI];
 #pragma unroll
   for (int j = 0; j < AI; ++j) {
     const int c = (wave * AI + j) * 64 + lane;
     const int r = c / CPR, cc = (c % CPR) ^ ((r / RPG) % CPR);
-    const int gr = min(m0 + r, P.M - 1);
-    a_off[j] = (uint32_t)gr * (uint32_t)P.K + cc * 8;
+    a_off[j] = (uint32_t)min(r, P.M - 1 - m0) * (uint32_t)P.K + cc * 8;
   }
 #pragma unroll
   for (int j = 0; j < BI; ++j) {
@@ -606,7 +607,7 @@ gemm_bf16_lds_kernel(GemmParams P) {
     const int k0 = (SPLIT ? kt0 + kt : kt) * BKT;
     bf16_t* st = S + (kt % STAGES) * STAGE;
     if (j < AI)
-      __builtin_amdgcn_global_load_lds((const void*)(P.A + a_off[j] + k0),
+      __builtin_amdgcn_global_load_lds((const void*)(a_tile + a_off[j] + k0),
                                        (lds_void_t*)(st + (wave * AI + j) * 64 * 8), 16, 0, 0);
     else
       __builtin_amdgcn_global_load_lds((const void*)(b_src[j - AI] + k0),
