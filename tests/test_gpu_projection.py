@@ -1,8 +1,8 @@
 """The selector's learned projections on the GPU: projected summaries and the
-selection from projected gate queries, bit-exact against the fp64 oracle, at
-row counts around the kernel's 64-row tiles and over several tiles per
-workgroup (rows past 4 x 1024 tiles' worth are covered by the case files'
-full-size runs; here the tile loop runs because few groups make it short)."""
+selection from projected gate queries, bit-exact against the fp64 oracle at
+row counts around the kernel's 64-row tiles (one tile per workgroup), and with
+two to four tiles per workgroup (2048 tiles and more over all sequences and
+groups) bit-equal to the same sequences one by one."""
 import numpy as np
 import pytest
 import torch
@@ -44,3 +44,21 @@ def test_projected_selection_is_exact(dtype, b, n, H, Hkv, dh, B, K):
         lg[:, :, :nf] = normalized_log_gate(ref["r"], ref["ct"], H // Hkv, dh)
         # scores are exact: the gate differs by its fp32 rounding and the fp32 sum of the normalizer
         assert_close_with_infs(out["log_gate"][i].cpu().numpy(), lg, dtype, "log_gate", tol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,b,n,dh,tiles", [("bf16", 4, 1090, 64, 2), ("bf16", 6, 1090, 128, 3),
+                                                ("f32", 8, 1090, 64, 4), ("f32", 4, 1037, 128, 2)])
+def test_several_tiles_per_workgroup(dtype, b, n, dh, tiles):
+    H = 32
+    print(f"\n[case] projection tiles {dtype} b={b} n={n} dh={dh}: {tiles} per workgroup", flush=True)
+    assert -(-n // 64) * b * H // 1024 == tiles and -(-n // 64) * H // 1024 == 0
+    w = configs.TINY.with_(dtype=dtype, batch=b, seq_len=n, n_heads=H, n_kv_heads=H, head_dim=dh, block_size=16,
+                           top_k=4, segments=(("txt", n),), index=91)
+    dev = [sas.to_device(a, dtype) for a in inputs.qkv(w)]
+    wgq = sas.to_device(inputs.normal(w, "w_gq", (H, dh, dh), 0.1), dtype)
+    cfg = sas.make_config(w, "gated")
+    out = sas.attention_prefill(cfg, *dev, wgq, log_gate=True, tau=True)
+    for i in range(b):
+        one = sas.attention_prefill(cfg, *(t[i:i + 1].contiguous() for t in dev), wgq, log_gate=True, tau=True)
+        for f in ("sel_idx", "log_gate", "tau"):
+            assert torch.equal(out[f][i], one[f][0]), (f, i)
