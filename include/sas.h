@@ -49,7 +49,7 @@ typedef enum {
   SAS_OK = 0,
   SAS_ERR_INVALID_ARGUMENT = -1, /* bad pointer, shape or config */
   SAS_ERR_UNSUPPORTED = -2,      /* valid but not implemented (e.g. head_dim 96) */
-  SAS_ERR_WORKSPACE = -3,        /* ws NULL or smaller than sas_workspace_size */
+  SAS_ERR_WORKSPACE = -3,        /* ws NULL or too small (see sas_workspace_size) */
   SAS_ERR_HIP = -4               /* a HIP launch or runtime call failed */
 } sas_status;
 
@@ -221,7 +221,13 @@ typedef struct {
   int32_t max_blocks;
 } sas_paged_kv;
 
-/* Bytes of scratch memory an entry point needs (0 on invalid config). */
+/* Bytes of scratch memory an entry point works best with (0 on invalid
+ * config); more is not used.  For SAS_OP_ATTENTION_BACKWARD the size never
+ * falls as batch, seq_len or top_k grow, so that a buffer for the largest call
+ * serves the smaller ones, and its last part (up to 1024 pieces of 512 head_dim
+ * bytes) only holds the sums of key tiles whose rows are divided over several
+ * workgroups: with less of it the call divides less, the same result but for
+ * the order of fp32 sums. */
 size_t sas_workspace_size(const sas_config* cfg, int32_t op, int32_t batch, int32_t seq_len);
 
 /* Selector + SAS attention over given Q/K/V (the scoring, Top-K, gating

@@ -180,6 +180,12 @@ struct Carve {
     off += align_up(bytes, 256);
     return p;
   }
+  // up to `want` pieces of `unit` bytes of what is left of `total` bytes (after
+  // check_ws of the rest): scratch that a call can do with less of
+  void* take_some(size_t total, size_t unit, long long& want) {
+    want = total > off ? std::min<long long>(want, (total - off) / unit) : 0;
+    return want > 0 ? take((size_t)want * unit) : nullptr;
+  }
 };
 
 // Does a product of M rows take the weight-streaming kernel?  Up to 64 rows the
@@ -568,9 +574,11 @@ struct BwdWs {
   int4* jobs;            // dK/dV jobs and the parts of divided key tiles (bf16, selections)
   int* job_count;
   int2* tile_part;
-  float* part;
-  BwdSplit split;
+  long long part_slots;  // parts wanted (their sums, bwd_part_bytes each, follow what is carved here)
 };
+
+size_t bwd_part_bytes(const sas_config* c) { return (size_t)2 * 64 * c->head_dim * 4; }
+
 
 BwdWs carve_backward(Carve& cv, const sas_config* c, int b, int n) {
   const size_t H = c->n_heads, Hkv = c->n_kv_heads, K = c->top_k > 0 ? c->top_k : 0;
@@ -588,11 +596,10 @@ BwdWs carve_backward(Carve& cv, const sas_config* c, int b, int n) {
   w.dlg_slots = (float*)cv.take((size_t)b * Hkv * n * K * 4);
   w.queue = (uint32_t*)cv.take(256);
   const bool lists = K > 0 && c->dtype == SAS_BF16 && c->mode != SAS_MODE_DENSE && !full_fwd(c);
-  w.split = lists ? bwd_split(b, c->n_kv_heads, n, c->block_size, c->top_k) : BwdSplit{0, 0};
-  w.jobs = lists ? (int4*)cv.take(((size_t)b * Hkv * ntk + w.split.slots) * sizeof(int4)) : nullptr;
+  w.part_slots = lists ? bwd_part_slots(b, c->n_kv_heads, n, c->block_size, c->top_k) : 0;
+  w.jobs = lists ? (int4*)cv.take(((size_t)b * Hkv * ntk + w.part_slots) * sizeof(int4)) : nullptr;
   w.job_count = lists ? (int*)cv.take(256) : nullptr;
   w.tile_part = lists ? (int2*)cv.take((size_t)b * Hkv * ntk * sizeof(int2)) : nullptr;
-  w.part = lists ? (float*)cv.take((size_t)w.split.slots * 2 * 64 * c->head_dim * 4) : nullptr;
   return w;
 }
 
@@ -765,7 +772,7 @@ size_t sas_workspace_size(const sas_config* c, int32_t op, int32_t batch, int32_
       break;
     case SAS_OP_ATTENTION_BACKWARD:
       if (seq_len <= 0 || check_config(c, false) != SAS_OK) return 0;
-      carve_backward(cv, c, batch, seq_len);
+      cv.take(carve_backward(cv, c, batch, seq_len).part_slots * bwd_part_bytes(c));
       break;
     case SAS_OP_SELECTOR_BACKWARD:
       if (seq_len <= 0 || check_config(c, false) != SAS_OK) return 0;
@@ -834,6 +841,7 @@ sas_status sas_attention_backward(const sas_config* c, int32_t batch, int32_t se
   Carve cv(ws);
   BwdWs bw = carve_backward(cv, c, batch, seq_len);
   SAS_TRY(check_ws(ws, ws_bytes, cv.off));
+  float* part = (float*)cv.take_some(ws_bytes, bwd_part_bytes(c), bw.part_slots);
   hipStream_t s = (hipStream_t)stream;
   const int Hkv = c->n_kv_heads;
   const int NB = (int)cdiv(seq_len, c->block_size);
@@ -878,9 +886,8 @@ sas_status sas_attention_backward(const sas_config* c, int32_t batch, int32_t se
   a.jobs = bw.jobs;
   a.job_count = bw.job_count;
   a.tile_part = bw.tile_part;
-  a.part = bw.part;
-  a.split_chunks = bw.split.chunks;
-  a.split_slots = bw.split.slots;
+  a.part = part;
+  a.part_slots = bw.part_slots;
   a.log_gate = gated ? in->log_gate : nullptr;
   a.outer = gated && c->gate_pos == SAS_GATE_OUTER;
   a.full = fullg;

@@ -708,26 +708,41 @@ __device__ __forceinline__ int block_scan1024(int v, int* wsum, int& all) {
 // passes: key tile by key tile (the longest lists first), (batch, group) pairs
 // inside.  cnt, off and tile_part are indexed [pair, tile].  One workgroup of
 // 1024 threads; each takes a contiguous range, then the ranges are offset.
-__global__ void __launch_bounds__(1024) bwd_jobs_kernel(const int* __restrict__ cnt, int Z, int ntiles, int chunks,
+// `slots`: parts that the scratch holds (see bwd_part_slots).
+__global__ void __launch_bounds__(1024) bwd_jobs_kernel(const int* __restrict__ cnt, int Z, int ntiles, int slots,
                                                         int* __restrict__ off, int4* __restrict__ jobs,
                                                         int* __restrict__ job_count, int2* __restrict__ tile_part) {
   __shared__ int wsum[16];
   const int T = Z * ntiles, tid = threadIdx.x;
   const int per = (T + 1023) / 1024, lo = min(T, tid * per), hi = min(T, lo + per);
-  auto parts_of = [&](int c) {  // parts of a tile of c rows
-    const int ch = (c + 63) / 64;  // chunks of the dK/dV pass
-    return ch > chunks ? (ch + chunks - 1) / chunks : 1;
-  };
-  int s_row = 0, s_job = 0, s_slot = 0;
+  int unit = slots > 0 ? BWD_PART_CHUNKS : 0x40000000;  // chunks (of the dK/dV pass) per part, at most
+  auto parts_of = [&](int c) { return max(1, ((c + 63) / 64 + unit - 1) / unit); };
+  int s_row = 0, s_job = 0, s_slot = 0, s_chunk = 0;
   for (int i = lo; i < hi; ++i) {
     const int c = cnt[(i % Z) * ntiles + i / Z], p = parts_of(c);
     s_row += c;
     s_job += p;
     s_slot += p > 1 ? p : 0;
+    s_chunk += (c + 63) / 64;
   }
-  int all, jobs_all;
+  int all, parts, jobs_all;
   int row = block_scan1024(s_row, wsum, all);
-  int slot = block_scan1024(s_slot, wsum, all);
+  int slot = block_scan1024(s_slot, wsum, parts);
+  if (parts > slots) {
+    int chunks;
+    block_scan1024(s_chunk, wsum, chunks);
+    const int last = (int)((2LL * chunks + slots - 1) / slots);  // fits: ceil(c / unit) < 2 c / unit where c > unit
+    do {
+      unit = (int)min((long long)last, max((long long)unit + 1, ((long long)unit * parts + slots - 1) / slots));
+      s_job = s_slot = 0;
+      for (int i = lo; i < hi; ++i) {
+        const int p = parts_of(cnt[(i % Z) * ntiles + i / Z]);
+        s_job += p;
+        s_slot += p > 1 ? p : 0;
+      }
+      slot = block_scan1024(s_slot, wsum, parts);
+    } while (parts > slots && unit < last);
+  }
   int job = block_scan1024(s_job, wsum, jobs_all);
   if (tid == 0) *job_count = jobs_all;
   for (int i = lo; i < hi; ++i) {
@@ -1132,13 +1147,14 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
     bwd_selmask_kernel<<<(unsigned)cdiv(rows * NW, 256), 256, 0, s>>>(P.sel, rows, P.K, NW, P.selmask);
     if (!fullatt) {
       // each tile's list of attending rows: counts, offsets, rows
-      if (!P.tile_rows || !P.tile_cnt || !P.tile_off || !P.jobs || !P.job_count || !P.tile_part || !P.part)
+      if (!P.tile_rows || !P.tile_cnt || !P.tile_off || !P.jobs || !P.job_count || !P.tile_part ||
+          (P.part_slots > 0 && !P.part))
         return hipErrorInvalidValue;
       const long long T = (long long)P.b * P.Hkv * ntk;
       if (T > INT32_MAX || rows * 2 * (P.K + 1) > (size_t)INT32_MAX) return hipErrorInvalidValue;
       const dim3 grid(ntk, P.Hkv, P.b);
       bwd_tile_rows_kernel<<<grid, 256, 0, s>>>(P.selmask, P.n, P.Hkv, P.B, NW, ntk, P.tile_cnt, nullptr, nullptr);
-      bwd_jobs_kernel<<<1, 1024, 0, s>>>(P.tile_cnt, P.b * P.Hkv, ntk, P.split_chunks, P.tile_off, P.jobs, P.job_count,
+      bwd_jobs_kernel<<<1, 1024, 0, s>>>(P.tile_cnt, P.b * P.Hkv, ntk, (int)P.part_slots, P.tile_off, P.jobs, P.job_count,
                                          P.tile_part);
       bwd_tile_rows_kernel<<<grid, 256, 0, s>>>(P.selmask, P.n, P.Hkv, P.B, NW, ntk, P.tile_cnt, P.tile_off,
                                                 P.tile_rows);
@@ -1164,7 +1180,7 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
   const bool lists = Q.tile_rows != nullptr;
   // list jobs are counted on the GPU: at most one per tile and one per slot
   const long long jq = (long long)cdiv(P.n, 128 / pg) * (P.H / pg) * P.b;
-  const long long jk = (long long)ntk * P.Hkv * P.b + (lists ? P.split_slots : 0);
+  const long long jk = (long long)ntk * P.Hkv * P.b + (lists ? P.part_slots : 0);
   const int rq = resident_workgroups(dq, 256), rk = resident_workgroups(dkv, 256);
   if (rq <= 0 || rk <= 0 || jq > INT32_MAX || jk > INT32_MAX) return hipErrorInvalidValue;
   if (jq > rq || jk > rk) fill_f32_kernel<<<1, 64, 0, s>>>((float*)P.queue, 2, 0.f);  // job counters to zero
@@ -1173,7 +1189,7 @@ static hipError_t launch_attention_backward_bf16(const BwdArgs& P, hipStream_t s
   if (jq > 0) dq<<<(unsigned)std::min<long long>(jq, rq), 256, 0, s>>>(A);
   A.queue = jk > rk ? P.queue + 1 : nullptr;
   if (jk > 0) dkv<<<(unsigned)std::min<long long>(jk, rk), 256, 0, s>>>(A);
-  if (lists) {
+  if (lists && P.part_slots > 0) {
     const unsigned tiles = (unsigned)ntk * P.Hkv * P.b;
     if (P.dh == 128)
       bwd_dkv_sum_kernel<128><<<tiles, 256, 0, s>>>(P.tile_part, P.part, P.n, P.Hkv, ntk, P.sm_scale, (bf16_t*)P.dK,

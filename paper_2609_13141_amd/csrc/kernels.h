@@ -209,14 +209,13 @@ struct BwdArgs {
   int* tile_off;
   int* tile_rows;
   // the dK/dV pass's jobs (bf16 path, selections): a tile's row list in one or
-  // several parts of about split_chunks chunks of 64 rows; parts of a divided
-  // tile leave fp32 sums in `part` and are added afterwards
-  int4* jobs;             // [b Hkv ceil(n/64) + split_slots] (tile, part, parts, slot of the part)
+  // several parts of whole chunks of 64 rows; parts of a divided tile leave fp32
+  // sums in `part` and are added afterwards
+  int4* jobs;             // [b Hkv ceil(n/64) + part_slots] (tile, part, parts, slot of the part)
   int* job_count;         // [1]
   int2* tile_part;        // [b, Hkv, ceil(n/64)] (parts, slot of the first)
-  float* part;            // [split_slots, 2, 64, dh] dK and dV of a part
-  int split_chunks;
-  long long split_slots;
+  float* part;            // [part_slots, 2, 64, dh] dK and dV of a part
+  long long part_slots;   // 0: no list is divided
   // gating formulation (GATED): outer gate; full scope; straight-through hard gate
   int outer, full, ste;
   float* dlog_gate_full;  // [b, Hkv, n, NB] output (full scope / straight-through)
@@ -229,23 +228,25 @@ constexpr int BWD_MAX_SEQ = 262144;
 // How the dK/dV pass divides its row lists.  A key tile is attended by its own
 // rows and by every row that selected one of its blocks, so early tiles have
 // lists several times the average and, with few (batch, group) pairs, one of
-// them alone takes longer than the rest.  Parts of about 1/2048 of all chunks
-// (four for each of the 512 resident workgroups) and at least 4 chunks keep the
-// last wave short; a divided tile has at most twice chunks / split_chunks
-// parts, which bounds the slots.  28/4 heads, 5003 tokens, K = 32 (316 tiles):
-// the pass 1311 -> 512 us (318 since its rows are staged once) and 31 us for adding the parts.
-struct BwdSplit {
-  int chunks;
-  long long slots;
-};
-inline BwdSplit bwd_split(int b, int Hkv, int n, int B, int K) {
-  const long long Z = (long long)b * Hkv, tiles = Z * ((n + 63) / 64);
+// them alone takes longer than the rest.  A tile of c chunks (of 64 rows) goes in
+// ceil(c / u) parts with the least u >= BWD_PART_CHUNKS whose parts fit the slots
+// of scratch (u = twice the chunks of all tiles over the slots always does),
+// whatever the selection and however few slots the caller's scratch has room for.
+// bwd_part_slots is what the pass works best with: BWD_MAX_PARTS, or what can be
+// divided at all, a tile j being at most ceil(n / 64) - j chunks long; it never
+// falls as b, n or K grow.  Whole attention backward with at most 512 / 1024 / 2048
+// parts (32, 64, 128 MiB at dh = 128): 28/4 heads, 5003 tokens, K = 32 (316 tiles)
+// 990 / 883 / 955 us; 32/32 heads, 2048 tokens, K = 16 (1024 tiles) 284 / 308 / 340.
+constexpr int BWD_PART_CHUNKS = 4;
+constexpr long long BWD_MAX_PARTS = 1024;
+inline long long bwd_part_slots(int b, int Hkv, int n, int B, int K) {
+  const long long Z = (long long)b * Hkv, ntk = (n + 63) / 64;
   const long long rows = Z * n * (K + 1) * (B > 64 ? 2 : 1);  // list entries, at most
-  const long long all = rows / 64 + tiles;
-  BwdSplit r;
-  r.chunks = (int)std::max<long long>(4, (all + 2047) / 2048);
-  r.slots = 2 * all / r.chunks + 1;
-  return r;
+  const long long cap = std::min(BWD_MAX_PARTS, 2 * (rows / 64 + Z * ntk) / BWD_PART_CHUNKS);
+  long long parts = 0;
+  for (long long c = BWD_PART_CHUNKS + 1; c <= ntk && parts < cap; ++c)
+    parts += Z * ((c + BWD_PART_CHUNKS - 1) / BWD_PART_CHUNKS);
+  return std::min(parts, cap);
 }
 hipError_t launch_attention_backward(int dtype, const BwdArgs& a, hipStream_t s);
 // p[0..n) = v with a kernel (capturable in a graph, unlike a memset node)

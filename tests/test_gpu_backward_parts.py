@@ -1,6 +1,7 @@
 """dK and dV of key tiles whose row list is divided into parts (few groups,
 long lists), next to tiles that are not, against the fp64 oracle.  A part is
-whole 32-row chunks; at these sizes one holds 8 of them."""
+whole chunks of 64 rows; at these sizes, with scratch for every part, it holds
+at most 4 of them."""
 import numpy as np
 import pytest
 import torch
@@ -36,7 +37,7 @@ def test_divided_row_lists(n, H, Hkv, dh, B, K, mode):
             m = set(range(64 * j // B, min(n - 1, 64 * j + 63) // B + 1))
             longest = max(longest, sum(t >= 64 * j and (t // B in m or bool(m & set(st["sel"][g, t].tolist())))
                                        for t in range(n)))
-    assert longest > 8 * 32, longest
+    assert longest > 4 * 64, longest
     dQ, dK, dV, _ = oracle.sas_attention_backward(f64(q[0]), f64(k[0]), f64(v[0]), f64(d_o[0]), B, mode, st["sel"],
                                                   st["log_gate"])
     assert_close(bw[0]["dq"][0].float().cpu().numpy(), dQ, "bf16", "dQ")
