@@ -222,12 +222,14 @@ typedef struct {
 } sas_paged_kv;
 
 /* Bytes of scratch memory an entry point works best with (0 on invalid
- * config); more is not used.  For SAS_OP_ATTENTION_BACKWARD the size never
- * falls as batch, seq_len or top_k grow, so that a buffer for the largest call
- * serves the smaller ones, and its last part (up to 1024 pieces of 512 head_dim
- * bytes) only holds the sums of key tiles whose rows are divided over several
- * workgroups: with less of it the call divides less, the same result but for
- * the order of fp32 sums. */
+ * config); more is not used.  The last part of it only holds partial sums of
+ * work that is divided over more workgroups: with less of that part the call
+ * divides less, the same result but for the order of fp32 sums.  It is up to
+ * 256 MiB of split products for SAS_OP_MLP and SAS_OP_LAYER, and up to 1024
+ * pieces of 512 head_dim bytes, of key tiles with long row lists, for
+ * SAS_OP_ATTENTION_BACKWARD.  For SAS_OP_MLP and SAS_OP_ATTENTION_BACKWARD the
+ * size never falls as batch, seq_len (tokens) or top_k grow, so that a buffer
+ * for the largest call serves the smaller ones. */
 size_t sas_workspace_size(const sas_config* cfg, int32_t op, int32_t batch, int32_t seq_len);
 
 /* Selector + SAS attention over given Q/K/V (the scoring, Top-K, gating

@@ -243,8 +243,9 @@ MlpWs carve_mlp(Carve& cv, const sas_config* c, size_t T) {
   return w;
 }
 
-// Scratch of the tiled products over T rows whose K is split (0 when none is):
-// the MLP's two and, with `attn`, the QKV and O projections; used one at a time.
+// Scratch that the tiled products over up to T rows whose K is split work best
+// with (0 when none is): the MLP's two and, with `attn`, the QKV and O
+// projections; used one at a time.
 size_t gemm_part_bytes(const sas_config* c, size_t T, bool attn) {
   size_t most = 0;
   auto product = [&](int epi, int N, int K) {
@@ -270,9 +271,11 @@ struct GemmPart {
   size_t bytes;
 };
 
-GemmPart carve_gemm_part(Carve& cv, const sas_config* c, size_t T, bool attn) {
-  const size_t n = gemm_part_bytes(c, T, attn);
-  return {n ? (float*)cv.take(n) : nullptr, n};
+// what is left of `total` bytes, up to that (SIZE_MAX: sizing)
+GemmPart carve_gemm_part(Carve& cv, size_t total, const sas_config* c, size_t T, bool attn) {
+  long long units = gemm_part_bytes(c, T, attn) / 256;
+  float* p = (float*)cv.take_some(total, 256, units);
+  return {p, (size_t)units * 256};
 }
 
 struct LayerWs {
@@ -286,7 +289,6 @@ struct LayerWs {
   void* h1;
   AttnWs att;
   MlpWs mlp;
-  GemmPart part;
 };
 
 LayerWs carve_layer(Carve& cv, const sas_config* c, int b, int n) {
@@ -304,7 +306,6 @@ LayerWs carve_layer(Carve& cv, const sas_config* c, int b, int n) {
   w.h1 = cv.take(T * c->d_model * ab);
   w.att = carve_attention(cv, c, b, n);
   w.mlp = carve_mlp(cv, c, T);
-  w.part = carve_gemm_part(cv, c, T, true);
   return w;
 }
 
@@ -785,11 +786,12 @@ size_t sas_workspace_size(const sas_config* c, int32_t op, int32_t batch, int32_
     case SAS_OP_MLP:
       if (check_config(c, true) != SAS_OK) return 0;
       carve_mlp(cv, c, (size_t)batch);
-      carve_gemm_part(cv, c, (size_t)batch, false);
+      carve_gemm_part(cv, SIZE_MAX, c, (size_t)batch, false);
       break;
     case SAS_OP_LAYER:
       if (seq_len <= 0 || check_config(c, true) != SAS_OK) return 0;
       carve_layer(cv, c, batch, seq_len);
+      carve_gemm_part(cv, SIZE_MAX, c, (size_t)batch * seq_len, true);
       break;
     case SAS_OP_DECODE:
       if (check_config(c, true) != SAS_OK || blocks_of(c, seq_len) > DSEL_MAX_BLOCKS) return 0;
@@ -1151,8 +1153,8 @@ sas_status sas_mlp_forward(const sas_config* c, int32_t tokens, const void* x, c
   SAS_TRY(check_weights(w, false, true));
   Carve cv(ws);
   MlpWs mw = carve_mlp(cv, c, (size_t)tokens);
-  const GemmPart part = carve_gemm_part(cv, c, (size_t)tokens, false);
   SAS_TRY(check_ws(ws, ws_bytes, cv.off));
+  const GemmPart part = carve_gemm_part(cv, ws_bytes, c, (size_t)tokens, false);
   return run_mlp(c, (size_t)tokens, x, w, y, mw, part, (hipStream_t)stream);
 }
 
@@ -1189,6 +1191,7 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   SAS_TRY(check_ws(ws, ws_bytes, cv.off));
   hipStream_t s = (hipStream_t)stream;
   const size_t T = (size_t)batch * seq_len;
+  const GemmPart part = carve_gemm_part(cv, ws_bytes, c, T, true);
   void* q = tp.q ? tp.q : lw.q;
   void* k = tp.k ? tp.k : lw.k;
   void* v = tp.v ? tp.v : lw.v;
@@ -1221,8 +1224,8 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   g.rope = lw.rope;
   // with a cache, the QKV product writes the K/V pages itself where it can
   const DecodeArgs da = cache ? decode_args(c, batch, nullptr, cache, w) : DecodeArgs{};
-  g.part = lw.part.p;
-  g.part_bytes = lw.part.bytes;
+  g.part = part.p;
+  g.part_bytes = part.bytes;
   g.prefill_cache = (cache && gemm_fills_cache(c->dtype, g)) ? &da : nullptr;
   {
     Timed tm("gemm_qkv", s);
@@ -1246,13 +1249,13 @@ sas_status sas_layer_forward(const sas_config* c, int32_t batch, int32_t seq_len
   og.N = c->d_model;
   og.resid = x;
   og.out = h1;
-  og.part = lw.part.p;
-  og.part_bytes = lw.part.bytes;
+  og.part = part.p;
+  og.part_bytes = part.bytes;
   {
     Timed tm("gemm_o", s);
     HIP_TRY(linear(c->dtype, og, s), "o-proj gemm");
   }
-  return run_mlp(c, T, h1, w, y, lw.mlp, lw.part, s);
+  return run_mlp(c, T, h1, w, y, lw.mlp, part, s);
 }
 
 size_t sas_decode_packed_bytes(const sas_config* c) {

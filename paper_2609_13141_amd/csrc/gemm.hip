@@ -949,11 +949,13 @@ static bool lds_shape(int epi, int K, int nlog, int npairs, int dh) {
 // 256x256), 600 x 4096 x 11008 119 -> 83 (80 tiles in 3 parts, not 160 whole ones
 // of 128x128), 3001 x 37888 x 3584 930 -> 788 (7 rounds of 256x256, not one of
 // them and 12 of 256x128), 3001 x 3584 x 18944 664 -> 454 (168 tiles in 3 parts).
+// A product of more than 1024 workgroups is not split (the last round is a small
+// share of four, and sums of 256 MiB a bound on the scratch).
 struct GemmPlan {
   int tile, splits;
   size_t bytes;  // scratch of the splits' sums
 };
-static GemmPlan gemm_plan(int M, int nlog, int K, bool may_split) {
+static GemmPlan gemm_plan(int M, int nlog, int K, size_t part_bytes) {
   static const struct {
     int bm, bn;
     double ns;
@@ -963,8 +965,8 @@ static GemmPlan gemm_plan(int M, int nlog, int K, bool may_split) {
   for (int t = 0; t < 4; ++t) {
     const long long tiles = (long long)cdiv(M, T[t].bm) * cdiv(nlog, T[t].bn);
     for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && (!may_split || K / 64 < 8 * sp || tiles > 512)) break;
       const size_t bytes = sp > 1 ? (size_t)tiles * sp * T[t].bm * T[t].bn * sizeof(float) : 0;
+      if (sp > 1 && (K / 64 < 8 * sp || tiles * sp > 1024 || bytes > part_bytes)) break;
       const double c = (double)((tiles * sp + 255) / 256) * K / sp * T[t].ns * 1e-3 +
                        (sp > 1 ? 8.0 + 2.0 * (double)bytes / 3.7e6 : 0.0);
       if ((t == 0 && sp == 1) || c < cost) {
@@ -980,7 +982,12 @@ size_t gemm_scratch_bytes(int dtype, const GemmArgs& g) {
   if (dtype != SAS_BF16 || g.M <= 0) return 0;
   const int npairs = g.epi == EPI_SWIGLU ? g.N : (g.epi == EPI_QKV_ROPE ? g.N / 2 : 0);
   const int nlog = g.epi == EPI_RESID ? g.N : (npairs + 31) / 32 * 64;
-  return lds_shape(g.epi, g.K, nlog, npairs, g.head_dim) ? gemm_plan(g.M, nlog, g.K, true).bytes : 0;
+  if (!lds_shape(g.epi, g.K, nlog, npairs, g.head_dim)) return 0;
+  // a plan depends on the rows' number of 128-row tiles; past 512 tiles of 256x256 none is split
+  size_t most = 0;
+  for (int i = 1; i <= cdiv(g.M, 128) && (long long)cdiv(i, 2) * cdiv(nlog, 256) <= 512; ++i)
+    most = std::max(most, gemm_plan(i * 128, nlog, g.K, SIZE_MAX).bytes);
+  return most;
 }
 
 static bool attrs_done = false;
@@ -1052,8 +1059,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   const long big_tiles = (long)((g.M + 255) / 256) * ((nlog + 255) / 256);
   if (g.epi == EPI_F32OUT) return hipErrorInvalidValue;  // bf16 fp32-output products go through gemv
   if (lds_shape(g.epi, g.K, nlog, npairs, g.head_dim)) {
-    GemmPlan plan = gemm_plan(g.M, nlog, g.K, g.part != nullptr);
-    if (plan.bytes > g.part_bytes) plan = gemm_plan(g.M, nlog, g.K, false);
+    const GemmPlan plan = gemm_plan(g.M, nlog, g.K, g.part ? g.part_bytes : 0);
     P.splits = plan.splits;
     switch (plan.tile) {
       case 0: return run_lds<256, 256, 2, 4, 2>(P, s);

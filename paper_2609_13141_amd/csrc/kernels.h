@@ -87,11 +87,12 @@ struct GemmArgs {
   // r / seq_len (only where gemm_fills_cache holds), or NULL
   const struct DecodeArgs* prefill_cache;
   // launch_gemm: scratch for products whose K is split over workgroups
-  // (gemm_scratch_bytes; NULL: not split)
+  // (gemm_scratch_bytes; with less they are split less, NULL: not at all)
   float* part;
   size_t part_bytes;
 };
-// Scratch that the product wants (0: it is not split).  Reads epi, M, N, K, head_dim.
+// The most scratch that the product works best with over all row counts up to M
+// (so that it never falls as M grows; 0: it is not split).  Reads epi, M, N, K, head_dim.
 size_t gemm_scratch_bytes(int dtype, const GemmArgs& a);
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // Does launch_gemm write the K/V pages of `a.prefill_cache` itself (the bf16

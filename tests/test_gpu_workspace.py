@@ -62,3 +62,23 @@ def test_attention_backward_with_less_scratch():
             assert_close(out[k].float().cpu().numpy(), best[k].numpy(), "bf16", k, tol=2 ** -8)
 
     shrink(full, run, check)
+
+
+@pytest.mark.parametrize("what", ["mlp", "layer"])
+def test_split_products_with_less_scratch(what):
+    T = 300
+    w = configs.L7B_1K.with_(seq_len=T, d_model=512, n_heads=4, n_kv_heads=2, d_ff=8192, segments=(("txt", T),),
+                             index=162)
+    print(f"\n[case] split products, shrinking workspace: {what}", flush=True)
+    cfg = sas.make_config(w, "dense")
+    W = sas.weights_to_device(inputs.layer_weights(w), "bf16")
+    x = sas.to_device(inputs.embeddings(w), "bf16")
+    if what == "mlp":
+        run = lambda ws: sas.mlp_forward(cfg, x, W, ws=ws)  # noqa: E731
+        full = sas.workspace_size(cfg, sas.OP_MLP, T, 0)
+    else:
+        run = lambda ws: sas.layer_forward(cfg, x, W, stats=False, ws=ws)["y"]  # noqa: E731
+        full = sas.workspace_size(cfg, sas.OP_LAYER, 1, T)
+    best = run(Fixed(full)).float().cpu().numpy()
+    # sums in another order before each product's rounding to bf16
+    shrink(full, run, lambda y: assert_close(y.float().cpu().numpy(), best, "bf16", what, tol=2 ** -7))

@@ -29,3 +29,16 @@ def test_attention_backward(H, Hkv, dh, B, K):
     assert size(cfg, 1, 256) - size(dense, 1, 256) < 1 << 16
     for b, n in ((1, 2048), (1, 16384), (4, 4096)):
         assert size(cfg, b, n) - size(dense, b, n) < 1024 * 2 * 64 * dh * 4 + (1 << 20)
+
+
+@pytest.mark.parametrize("d,F,H,Hkv", [(4096, 11008, 32, 32), (3584, 18944, 28, 4), (1536, 8960, 12, 2), (256, 688, 4, 4)])
+def test_products(d, F, H, Hkv):
+    w = configs.L7B_1K.with_(d_model=d, d_ff=F, n_heads=H, n_kv_heads=Hkv)
+    cfg = sas.make_config(w)
+    mlp = [sas.workspace_size(cfg, sas.OP_MLP, n, 0) for n in range(1, 20000, 61)]
+    assert never_falls(mlp)
+    # activations [n, d] and [n, d_ff], and at most 256 MiB of sums
+    for n, s in zip(range(1, 20000, 61), mlp):
+        assert s <= 2 * n * (d + F) + 512 + (256 << 20)
+    # (from 1024 query tiles on, the layer's attention no longer splits its keys)
+    assert never_falls([sas.workspace_size(cfg, sas.OP_LAYER, 1, n) for n in range(1, 128 * (1023 // H), 61)])
