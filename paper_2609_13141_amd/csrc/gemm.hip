@@ -38,6 +38,7 @@ struct GemmParams {
   // gemm_finish_kernel adds them and runs the epilogue
   int splits;
   float* part;
+  int n_off, n_cnt;  // gemm_bf16_lds_kernel: logical columns [n_off, n_off + n_cnt) of this launch
 };
 
 // Tile of workgroup `bid`.  Workgroups are dispatched round-robin over the 8
@@ -565,7 +566,7 @@ gemm_bf16_lds_kernel(GemmParams P) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int Mt = (P.M + BM - 1) / BM, Nt = (P.N + BN - 1) / BN;
+  const int Mt = (P.M + BM - 1) / BM, Nt = (P.n_cnt + BN - 1) / BN;
   // SPLIT: workgroup (split, tile) in one order, split by split, so that the tiles
   // an XCD works on at a time share operands over the same part of K
   int mt, nt, kt0 = 0, nk = P.K / BKT;
@@ -581,7 +582,7 @@ gemm_bf16_lds_kernel(GemmParams P) {
   } else {
     tile_of(blockIdx.x, Mt, Nt, P.group_m, mt, nt);
   }
-  const int m0 = mt * BM, n0 = nt * BN;
+  const int m0 = mt * BM, n0 = P.n_off + nt * BN;
 
   // per-lane sources of the direct-to-LDS loads (rows clamped; results of
   // clamped rows are never stored); A's offsets count from the tile's first row,
@@ -895,7 +896,7 @@ static hipError_t run_bf16(const GemmParams& P, hipStream_t s) {
 template <int EPI, int BM, int BN, int WM, int WN, int STAGES, bool SPLIT>
 static hipError_t run_lds_t(const GemmParams& P, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
-  const int tiles = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
+  const int tiles = ((P.M + BM - 1) / BM) * ((P.n_cnt + BN - 1) / BN);
   const size_t lds = (size_t)STAGES * (BM + BN) * 64 * sizeof(bf16_t);
   static bool attr = false;
   if (!attr) {
@@ -943,37 +944,51 @@ static bool lds_shape(int epi, int K, int nlog, int npairs, int dh) {
 // steps whose time depends on the tile alone (ns per k with every unit busy,
 // measured at M = 300 .. 3000, K = 3584 .. 18944: 256x256 25.5, 128x256 15.0,
 // 256x128 14.7, 128x128 9.8: the larger the tile, the fewer operand bytes per
-// product).  Splits add a launch and their sums' way through memory (8 us, and
-// 8 bytes per sum at 3.7 TB/s).  The plan with the least of that, in us under the
+// product).  Splits add a launch (8 us) and their sums' way through memory: 4 bytes
+// per sum written at 3.7 TB/s, and read by one workgroup per tile, 55 GB/s each.
+// Over 64 .. 3072 rows of the 7B, 28/4 and d = 1536 layers the plan is within 0.3%
+// of the best one measured on average and 10% at worst.  The plan with the least of that, in us under the
 // profiler: 600 x 12288 x 4096 113 -> 78 (240 tiles of 128x256, not 144 of
 // 256x256), 600 x 4096 x 11008 119 -> 83 (80 tiles in 3 parts, not 160 whole ones
 // of 128x128), 3001 x 37888 x 3584 930 -> 788 (7 rounds of 256x256, not one of
 // them and 12 of 256x128), 3001 x 3584 x 18944 664 -> 454 (168 tiles in 3 parts).
+// Where 256x256 tiles would fill one round and little of a second, one round of
+// them followed by 256x128 tiles for the other columns is another plan, taken if
+// it is 4% better (two launches: 3% better by this count was 3% slower).  7B
+// gate/up product at 1000 rows (344 tiles of 256x256): 161 us, one launch 173.
 // A product of more than 1024 workgroups is not split (the last round is a small
 // share of four, and sums of 256 MiB a bound on the scratch).
 struct GemmPlan {
   int tile, splits;
   size_t bytes;  // scratch of the splits' sums
+  int first;     // columns that a first launch of 256x256 tiles takes
 };
 static GemmPlan gemm_plan(int M, int nlog, int K, size_t part_bytes) {
   static const struct {
     int bm, bn;
     double ns;
   } T[4] = {{256, 256, 25.5}, {128, 256, 15.0}, {256, 128, 14.7}, {128, 128, 9.8}};
-  GemmPlan best = {0, 1, 0};
+  GemmPlan best = {0, 1, 0, 0};
   double cost = 0.0;
   for (int t = 0; t < 4; ++t) {
     const long long tiles = (long long)cdiv(M, T[t].bm) * cdiv(nlog, T[t].bn);
     for (int sp = 1; sp <= 8; ++sp) {
       const size_t bytes = sp > 1 ? (size_t)tiles * sp * T[t].bm * T[t].bn * sizeof(float) : 0;
       if (sp > 1 && (K / 64 < 8 * sp || tiles * sp > 1024 || bytes > part_bytes)) break;
-      const double c = (double)((tiles * sp + 255) / 256) * K / sp * T[t].ns * 1e-3 +
-                       (sp > 1 ? 8.0 + 2.0 * (double)bytes / 3.7e6 : 0.0);
+      double c = (double)((tiles * sp + 255) / 256) * K / sp * T[t].ns * 1e-3;
+      if (sp > 1)
+        c += 8.0 + (double)bytes / 3.7e6 + (double)((tiles + 255) / 256) * sp * T[t].bm * T[t].bn * 4 / 55e3;
       if ((t == 0 && sp == 1) || c < cost) {
         cost = c;
-        best = {t, sp, bytes};
+        best = {t, sp, bytes, 0};
       }
     }
+  }
+  const int mt = cdiv(M, 256), full = 256 / mt * 256;  // columns of one round of 256x256 tiles
+  if (full > 0 && full < nlog) {
+    const long long rest = (long long)mt * cdiv(nlog - full, 128);
+    const double c = K * T[0].ns * 1e-3 + (double)((rest + 255) / 256) * K * T[2].ns * 1e-3;
+    if (c < 0.96 * cost) best = {2, 1, 0, full};
   }
   return best;
 }
@@ -1048,6 +1063,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   P.group_m = (g.epi == EPI_RESID && g.K > 2 * nlog) ? 2 : 8;
   P.splits = 1;
   P.part = g.part;
+  P.n_off = 0;
+  P.n_cnt = nlog;
   P.seq_len = g.seq_len;
   P.rope = g.rope;
   P.row_pos = g.row_pos;
@@ -1061,6 +1078,14 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   if (lds_shape(g.epi, g.K, nlog, npairs, g.head_dim)) {
     const GemmPlan plan = gemm_plan(g.M, nlog, g.K, g.part ? g.part_bytes : 0);
     P.splits = plan.splits;
+    if (plan.first > 0) {
+      g_launch_events = LaunchEvents{nullptr, nullptr, 0};  // two launches: timed around both
+      P.n_cnt = plan.first;
+      const hipError_t e = run_lds<256, 256, 2, 4, 2>(P, s);
+      if (e != hipSuccess) return e;
+      P.n_off = plan.first;
+      P.n_cnt = nlog - plan.first;
+    }
     switch (plan.tile) {
       case 0: return run_lds<256, 256, 2, 4, 2>(P, s);
       case 1: return run_lds<128, 256, 2, 4, 3>(P, s);

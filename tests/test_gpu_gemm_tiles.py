@@ -18,12 +18,14 @@ def draw(seed):
 
 
 # (tokens, d, d_ff): the tiles and splits of gate/up and down that the launch takes there
-MLP = [(65, 256, 4096),     # 128x128; 128x128 in 8
+MLP = [(65, 256, 4096),     # 128x128; 128x128 in 6
        (130, 2048, 256),    # 128x128 in several; 128x128
        (200, 1096, 2056),   # columns that end inside a tile (and K % 64 != 0: the register-staged kernel)
        (700, 2048, 8192),   # 256x256; 256x128 in 5
-       (2100, 1024, 8192),  # 256x128 or larger; 128x256 in 3
+       (2100, 1024, 8192),  # one round of 256x256 and 256x128 for the other columns; 256x128 in 3
        (1300, 3584, 8192),  # 256x128; 256x256 in 3
+       (700, 256, 11000),   # one round of 256x256 and 256x128 for the other columns, ragged; K % 64 != 0
+       (520, 3072, 12288),  # 128x256 in 4
        (300, 128, 128)]
 
 
@@ -45,7 +47,8 @@ def test_mlp_tiles(T, d, F):
 
 
 @pytest.mark.parametrize("b,n,d,H,Hkv,dh", [(1, 100, 2048, 4, 2, 64), (2, 75, 4096, 2, 1, 128), (3, 150, 512, 7, 1, 128),
-                                            (1, 600, 3072, 16, 4, 128)])
+                                            (1, 600, 3072, 16, 4, 128),
+                                            (1, 1400, 256, 64, 16, 128)])  # the last in two launches of columns
 def test_qkv_tiles(b, n, d, H, Hkv, dh):
     print(f"\n[case] qkv tiles b={b} n={n} d={d} H={H}/{Hkv} dh={dh}", flush=True)
     r = draw(n)
