@@ -1279,12 +1279,15 @@ __global__ void __launch_bounds__(256) selector_ds_kernel(const int32_t* __restr
         slot_s[wave][r][lane] = 0.f;
       }
     }
-    if (!dfull) {  // a wave's LDS accesses complete in order
+    if (!dfull) {
+      wave_lds_fence();
 #pragma unroll
       for (int r = 0; r < DS_ROWS; ++r)
         if (sk[r] >= m0 && sk[r] < m0 + 64) atomicAdd(&slot_s[wave][r][sk[r] - m0], dk[r]);
+      wave_lds_fence();
 #pragma unroll
       for (int r = 0; r < DS_ROWS; ++r) dl[r] = slot_s[wave][r][lane];
+      wave_lds_fence();  // before the next blocks' zeros
     }
 #pragma unroll
     for (int r = 0; r < DS_ROWS; ++r) {

@@ -40,6 +40,16 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Between LDS writes of a wave's lanes and reads of the same values by other
+// lanes of the wave.  The hardware completes a wave's LDS accesses in order; this
+// keeps the compiler from moving the reads (of another type, or past an atomic)
+// before the writes.  No instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // LDS tiles of the attention kernels: rows of DH values without padding, the 16-byte
 // chunks of row r at positions c ^ lds_swz(r).  16 consecutive rows of one chunk
 // (the row-major operand reads) then lie in distinct banks, and so do the four

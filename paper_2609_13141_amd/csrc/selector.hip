@@ -164,10 +164,12 @@ __global__ void __launch_bounds__(256) project_rows_kernel(const T* __restrict__
     // accumulator element i of column block t: row q + 4 i, column 16 t + c;
     // back through the wave's own LDS rows (its reads above are done) to 16-byte stores
     T* ow = As + wave * 16 * PITCH;
+    wave_lds_fence();
 #pragma unroll
     for (int t = 0; t < DH / 16; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) ow[(q + 4 * i) * PITCH + t * 16 + c] = Act<T>::from_f64(acc[t][i]);
+    wave_lds_fence();
     constexpr int CW = 16 / (int)sizeof(T);  // values per 16-byte store
 #pragma unroll
     for (int k = 0; k < 16 * DH / CW / 64; ++k) {
