@@ -949,13 +949,15 @@ static bool lds_shape(int epi, int K, int nlog, int npairs, int dh) {
 // measured at M = 300 .. 3000, K = 3584 .. 18944: 256x256 25.5, 128x256 15.0,
 // 256x128 14.7, 128x128 9.8: the larger the tile, the fewer operand bytes per
 // product).  Splits add a launch (8 us) and their sums' way through memory: 4 bytes
-// per sum written at 3.7 TB/s, and read by one workgroup per tile, 55 GB/s each.
-// Over 64 .. 3072 rows of the 7B, 28/4 and d = 1536 layers the plan is within 0.3%
-// of the best one measured on average and 10% at worst.  The plan with the least of that, in us under the
-// profiler: 600 x 12288 x 4096 113 -> 78 (240 tiles of 128x256, not 144 of
-// 256x256), 600 x 4096 x 11008 119 -> 83 (80 tiles in 3 parts, not 160 whole ones
-// of 128x128), 3001 x 37888 x 3584 930 -> 788 (7 rounds of 256x256, not one of
-// them and 12 of 256x128), 3001 x 3584 x 18944 664 -> 454 (168 tiles in 3 parts).
+// per sum written at 3.4 TB/s and read at 3.7, or by one workgroup per tile at 55
+// GB/s each where that takes longer (few large tiles).  Over 25 row counts from 66
+// to 8192 of the 7B, 28/4 and d = 1536 layers (300 products) the plan takes 0.8%
+// longer than the best tile and split measured on average, 14% at worst.  In us
+// under the profiler, against the fixed rule before: 600 x 12288 x 4096 113 -> 78
+// (240 tiles of 128x256, not 144 of 256x256), 600 x 4096 x 11008 119 -> 83 (80
+// tiles in 3 parts, not 160 whole ones of 128x128), 3001 x 37888 x 3584 930 -> 788
+// (7 rounds of 256x256, not one of them and 12 of 256x128), 3001 x 3584 x 18944
+// 664 -> 454 (168 tiles in 3 parts).
 // Where 256x256 tiles would fill one round and little of a second, one round of
 // them followed by 256x128 tiles for the other columns is another plan, taken if
 // it is 4% better (two launches: 3% better by this count was 3% slower).  7B
@@ -981,7 +983,8 @@ static GemmPlan gemm_plan(int M, int nlog, int K, size_t part_bytes) {
       if (sp > 1 && (K / 64 < 8 * sp || tiles * sp > 1024 || bytes > part_bytes)) break;
       double c = (double)((tiles * sp + 255) / 256) * K / sp * T[t].ns * 1e-3;
       if (sp > 1)
-        c += 8.0 + (double)bytes / 3.7e6 + (double)((tiles + 255) / 256) * sp * T[t].bm * T[t].bn * 4 / 55e3;
+        c += 8.0 + (double)bytes / 3.4e6 +
+             std::max((double)bytes / 3.7e6, (double)((tiles + 255) / 256) * sp * T[t].bm * T[t].bn * 4 / 55e3);
       if ((t == 0 && sp == 1) || c < cost) {
         cost = c;
         best = {t, sp, bytes, 0};

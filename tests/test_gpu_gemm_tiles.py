@@ -22,7 +22,7 @@ MLP = [(65, 256, 4096),     # 128x128; 128x128 in 6
        (130, 2048, 256),    # 128x128 in several; 128x128
        (200, 1096, 2056),   # columns that end inside a tile (and K % 64 != 0: the register-staged kernel)
        (700, 2048, 8192),   # 256x256; 256x128 in 5
-       (2100, 1024, 8192),  # one round of 256x256 and 256x128 for the other columns; 256x128 in 3
+       (2100, 1024, 8192),  # one round of 256x256 and 256x128 for the other columns; 128x256 in 3
        (1300, 3584, 8192),  # 256x128; 256x256 in 3
        (700, 256, 11000),   # one round of 256x256 and 256x128 for the other columns, ragged; K % 64 != 0
        (520, 3072, 12288),  # 128x256 in 4
